@@ -5,14 +5,17 @@ shapes/dtypes/devices the C ABI cannot see (it receives raw pointers), converts
 handles, and raises RVError on any non-zero rv_status.  Tensors are torch CUDA
 (HIP) tensors; bf16 tensors may be any 2-byte dtype (bfloat16, int16, uint16) since
 only their bits matter.  PyTorch supplies device memory and streams, nothing else.
-There is no fallback: if librv.so is missing the import of this module fails.
+There is no fallback: if librv.so or the marshalling module _rv_bind.so is missing the
+import of this module fails.
 """
 import ctypes
+import importlib.util
 import os
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
+BIND_PATH = os.path.join(_HERE, "_rv_bind.so")
 LIB_PATH = os.path.join(_HERE, "librv.so")
 SYNTH_LIB_PATH = os.path.join(_HERE, "librv_synth.so")
 
@@ -42,6 +45,7 @@ def _load():
         raise ImportError(f"{LIB_PATH} is not built; run __graft_entry__.build() "
                           "(hipcc --offload-arch=gfx950)")
     lib = ctypes.CDLL(LIB_PATH)
+    # (an array of pointers is a vp: it goes as the bytes that _rv_bind packs, or as a ctypes array)
     vp, i32, i64 = ctypes.c_void_p, ctypes.c_int, ctypes.c_int64
     P = ctypes.POINTER
     sigs = {
@@ -62,18 +66,18 @@ def _load():
         "rv_mem_load": ([vp, ctypes.c_char_p], i32),
         "rv_attend_frame": ([vp, vp, vp, i32, vp, vp, i64, i64, i32, i32, P(rv_qsub), vp, vp, vp, vp], i32),
         "rv_attend_frame_fused": ([vp, vp, vp, i32, vp, vp, i64, i64, i32, i32, P(rv_qsub), vp, vp, vp, vp], i32),
-        "rv_admit_layers_tiled": ([i32, P(vp), i32, i32, P(vp), P(vp), P(vp), i32, P(vp), P(vp), vp], i32),
+        "rv_admit_layers_tiled": ([i32, vp, i32, i32, vp, vp, vp, i32, vp, vp, vp], i32),
         "rv_attend_frame_noalloc": ([vp, vp, vp, i32, vp, vp, i64, i64, i32, i32, P(rv_qsub), vp, vp, vp, vp],
                                     i32),
         "rv_admit": ([vp, i32, vp, vp, i32, vp, i32, vp, vp], i32),
-        "rv_admit_layers": ([i32, P(vp), P(vp), P(vp), P(vp), i32, P(rv_qsub), i32, P(vp), i32, P(vp), P(vp), vp], i32),
-        "rv_admit_layers_shared": ([i32, P(vp), P(vp), P(vp), P(vp), i32, P(rv_qsub), i32, P(vp), i32, P(vp), P(vp),
+        "rv_admit_layers": ([i32, vp, vp, vp, vp, i32, P(rv_qsub), i32, vp, i32, vp, vp, vp], i32),
+        "rv_admit_layers_shared": ([i32, vp, vp, vp, vp, i32, P(rv_qsub), i32, vp, i32, vp, vp,
                                     vp], i32),
         "rv_mem_stage": ([vp, i32, P(vp), P(vp), P(i64), vp], i32),
         "rv_mem_stage_frame": ([vp, vp, vp, i32, vp], i32),
-        "rv_mem_stage_frames": ([i32, P(vp), P(vp), P(vp), i32, vp], i32),
+        "rv_mem_stage_frames": ([i32, vp, vp, vp, i32, vp], i32),
         "rv_attend_staged": ([vp, i32, vp, P(rv_qsub), vp, vp, vp, vp], i32),
-        "rv_admit_staged_layers": ([i32, P(vp), P(vp), i32, P(rv_qsub), i32, P(vp), i32, P(vp), P(vp), vp], i32),
+        "rv_admit_staged_layers": ([i32, vp, vp, i32, P(rv_qsub), i32, vp, i32, vp, vp, vp], i32),
         "rv_reserve_workspace": ([i32, i32, i64, i32], i32),
         "rv_attention_plan": ([i32, i32, i64, i32, i32, i32, P(rv_attn_plan)], i32),
         "rv_device_status": ([], i32),
@@ -85,7 +89,17 @@ def _load():
     return lib
 
 
+def _load_bind():
+    if not os.path.exists(BIND_PATH):
+        raise ImportError(f"{BIND_PATH} is not built; run __graft_entry__.build()")
+    spec = importlib.util.spec_from_file_location("paper_2609_23286_amd._rv_bind", BIND_PATH)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
 _lib = _load()
+_bind = _load_bind()
 
 
 def lib():
@@ -99,17 +113,18 @@ def _check(status):
 
 def _stream(stream):
     if stream is None:
-        return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
     return ctypes.c_void_p(int(stream))
 
 
-def _ptr(t, shape=None, itemsize=None, what="tensor"):
+def _ptr_python(t, shape=None, itemsize=None, what="tensor"):
+    """Address of a device tensor argument, or None; raises on one the C ABI cannot take."""
     if t is None:
         return None
     if isinstance(t, int):
-        return ctypes.c_void_p(t)
+        return t
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{what}: expected a torch tensor")
     if not t.is_cuda:
@@ -120,7 +135,24 @@ def _ptr(t, shape=None, itemsize=None, what="tensor"):
         raise TypeError(f"{what}: element size {t.element_size()}, expected {itemsize}")
     if shape is not None and tuple(t.shape) != tuple(shape):
         raise ValueError(f"{what}: shape {tuple(t.shape)}, expected {tuple(shape)}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+# The same checks on plain tensors without Python's attribute calls: one address, and the
+# addresses of a list of tensors (one per layer) as bytes.
+_bind.setup(_ptr_python, ctypes.cast(_lib.rv_mem_view, ctypes.c_void_p).value,
+            ctypes.cast(_lib.rv_mem_len, ctypes.c_void_p).value)
+_ptr, _ptrs = _bind.ptr, _bind.ptrs
+
+
+def _mem_state(mem):
+    """(memK, memV, head stride, length) of a memory, as rv_mem_view and rv_mem_len give them."""
+    if type(mem) is not Memory:
+        return (*mem.view(), mem.len)
+    st = _bind.mem_state(mem.handle.value if mem.handle else None)
+    if isinstance(st, int):
+        _check(st)
+    return st
 
 
 def version():
@@ -254,8 +286,7 @@ def attend_frame(Q, K, V, mem, out, lse, saliency=None, qs=None, stream=None,
     ``memK``/``memV`` device pointers (int or tensor), ``mem_len`` and ``head_stride``."""
     N, H, d = Q.shape
     if mem is not None:
-        mk, mv, hs = mem.view()
-        ml = mem.len
+        mk, mv, hs, ml = _mem_state(mem)
     else:
         mk = memK.data_ptr() if isinstance(memK, torch.Tensor) else (memK or 0)
         mv = memV.data_ptr() if isinstance(memV, torch.Tensor) else (memV or 0)
@@ -263,8 +294,7 @@ def attend_frame(Q, K, V, mem, out, lse, saliency=None, qs=None, stream=None,
     shp = (N, H, d)
     q = qs if qs is None or isinstance(qs, rv_qsub) else rv_qsub(*qs)
     _check(_lib.rv_attend_frame(
-        _ptr(Q, shp, 2, "Q"), _ptr(K, shp, 2, "K"), _ptr(V, shp, 2, "V"), N,
-        ctypes.c_void_p(mk), ctypes.c_void_p(mv), ml, hs, H, d,
+        _ptr(Q, shp, 2, "Q"), _ptr(K, shp, 2, "K"), _ptr(V, shp, 2, "V"), N, mk, mv, ml, hs, H, d,
         ctypes.byref(q) if q is not None else None,
         _ptr(out, shp, 2, "out"), _ptr(lse, (H, N), 4, "lse"),
         _ptr(saliency, (H, N), 4, "saliency"), _stream(stream)))
@@ -277,12 +307,11 @@ def attend_frame_fused(Q, K, V, mem, out, lse, sal_tiles, qs, stream=None):
     """rv_attend_frame_fused: attention with the saliency formed in its epilogue, per
     128-query block: sal_tiles [H, ceil(N / 128), N] fp32."""
     N, H, d = Q.shape
-    mk, mv, hs = mem.view()
+    mk, mv, hs, ml = _mem_state(mem)
     shp = (N, H, d)
     q = qs if isinstance(qs, rv_qsub) else rv_qsub(*qs)
     _check(_lib.rv_attend_frame_fused(
-        _ptr(Q, shp, 2, "Q"), _ptr(K, shp, 2, "K"), _ptr(V, shp, 2, "V"), N, ctypes.c_void_p(mk),
-        ctypes.c_void_p(mv), mem.len, hs, H, d, ctypes.byref(q), _ptr(out, shp, 2, "out"),
+        _ptr(Q, shp, 2, "Q"), _ptr(K, shp, 2, "K"), _ptr(V, shp, 2, "V"), N, mk, mv, ml, hs, H, d, ctypes.byref(q), _ptr(out, shp, 2, "out"),
         _ptr(lse, (H, N), 4, "lse"), _ptr(sal_tiles, (H, -(-N // QUERY_BLOCK), N), 4, "sal_tiles"),
         _stream(stream)))
 
@@ -295,7 +324,7 @@ def admit_layers_tiled(sal_tiles, budget, K, V, mems, frame_id, saliency_out=Non
     arr = ctypes.c_void_p * L
 
     def pack(ts, shape, itemsize, what):
-        return arr(*[_ptr(t, shape, itemsize, f"{what}[{i}]") for i, t in enumerate(ts)])
+        return _ptrs(ts, L, shape, itemsize, what)
 
     sal = pack(saliency_out, (H, N), 4, "saliency_out") if saliency_out is not None else None
     idx = pack(idx_out, (H, budget), 4, "idx_out") if idx_out is not None else None
@@ -322,7 +351,7 @@ def admit_staged_layers(Q, lse, qs, budget, mems, frame_id, saliency_out=None, i
     arr = ctypes.c_void_p * L
 
     def pack(ts, shape, itemsize, what):
-        return arr(*[_ptr(t, shape, itemsize, f"{what}[{i}]") for i, t in enumerate(ts)])
+        return _ptrs(ts, L, shape, itemsize, what)
 
     q = qs if isinstance(qs, rv_qsub) else rv_qsub(*qs)
     sal = pack(saliency_out, (H, N), 4, "saliency_out") if saliency_out is not None else None
@@ -351,7 +380,7 @@ def admit_layers(Q, K, V, lse, qs, budget, mems, frame_id, saliency_out=None, id
     arr = ctypes.c_void_p * L
 
     def pack(ts, shape, itemsize, what):
-        return arr(*[_ptr(t, shape, itemsize, f"{what}[{i}]") for i, t in enumerate(ts)])
+        return _ptrs(ts, L, shape, itemsize, what)
 
     q = qs if isinstance(qs, rv_qsub) else rv_qsub(*qs)
     sal = pack(saliency_out, (H, N), 4, "saliency_out") if saliency_out is not None else None
@@ -371,8 +400,7 @@ def stage_frames(mems, K, V, stream=None):
     shp = (N, mems[0].n_heads, HEAD_DIM)
     arr = ctypes.c_void_p * L
     _check(_lib.rv_mem_stage_frames(L, arr(*[m.handle for m in mems]),
-                                    arr(*[_ptr(k, shp, 2, f"K[{i}]") for i, k in enumerate(K)]),
-                                    arr(*[_ptr(v, shp, 2, f"V[{i}]") for i, v in enumerate(V)]), N,
+                                    _ptrs(K, L, shp, 2, "K"), _ptrs(V, L, shp, 2, "V"), N,
                                     _stream(stream)))
 
 # ---- seeded stream generator on the GPU (benchmark inputs) -------------------------
@@ -402,13 +430,13 @@ def gpu_frame_qkv(cfg, frame, out, layer0=0, n_layers=None, stream=None):
     shape = (n_layers, 3, cfg.n_tokens, cfg.n_heads, cfg.head_dim)
     rc = _load_synth().rvs_frame_qkv(cfg.seed, frame & 0xFFFFFFFF, layer0, n_layers, cfg.n_tokens, cfg.n_heads,
                                      cfg.head_dim, cfg.sigma, cfg.n_plant, cfg.alpha, cfg.lognormal_sigma,
-                                     _ptr(out, shape, 2, "out"), _stream(stream))
+                                     _ptr_python(out, shape, 2, "out"), _stream(stream))
     if rc != 0:
         raise RVError(rc, "rvs_frame_qkv failed")
 
 
 def gpu_normal(seed, frame, layer, tag, out, sigma, stream=None):
     rc = _load_synth().rvs_normal_bf16(seed, frame & 0xFFFFFFFF, layer, tag, out.numel(), sigma,
-                                       _ptr(out, None, 2, "out"), _stream(stream))
+                                       _ptr_python(out, None, 2, "out"), _stream(stream))
     if rc != 0:
         raise RVError(rc, "rvs_normal_bf16 failed")
