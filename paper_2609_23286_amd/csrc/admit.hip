@@ -19,13 +19,13 @@
 // select_kernel (Sec. 3.3 Eq. 6, head-specific retention): one workgroup per
 // (layer, head) takes the `budget` largest S_j, equal values ordered by lower index.
 // The order is that of the 64-bit key (bits of S, ~j): fp32 bit patterns order like
-// the values for S >= 0.  Budgets up to kWaveTopK: each wave extracts the top `budget`
-// of its quarter by repeated wave-wide maxima, and one wave extracts the top `budget` of
-// the 4 x budget candidates the same way.  Larger budgets: an MSB-first radix select
-// over the bit patterns finds the threshold value and how many of its ties to take, and
-// block scans emit the indices.  Either way the indices come out ascending and the
-// chosen K/V rows are copied to the memory arena at rows mem_len.. with their
-// provenance.
+// the values for S >= 0.  Budgets up to kRankedBudget of frames up to kRankedTokens tokens:
+// a lower bound of the budget-th largest value, from the threads' own maxima, leaves a few
+// candidates, which are ranked by counting.  Others, and frames whose ties leave too many
+// candidates: an MSB-first radix select over the bit patterns finds the threshold value and
+// how many of its ties to take, and block scans emit the indices.  Either way the indices
+// come out ascending and the chosen K/V rows are copied to the memory arena at rows
+// mem_len.. with their provenance.
 #include <type_traits>
 
 #include "rv_internal.h"
@@ -377,101 +377,156 @@ __device__ __forceinline__ uint64_t rank_key(float v, int j) {
 }
 
 template <int CTRL>
-__device__ __forceinline__ uint32_t max_dpp(uint32_t x) {
-  return max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false));
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, false);
 }
 
-// The larger value of the pair a v_permlane*_swap leaves: the two lanes' values, in some
-// order on every lane.
-template <class Pair>
-__device__ __forceinline__ uint32_t pair_max(const Pair& p) {
-  return max((uint32_t)p[0], (uint32_t)p[1]);
+// x of lane l ^ 16, and of lane l ^ 32: a v_permlane*_swap of x with itself leaves the two
+// lanes' values in some order on every lane.
+__device__ __forceinline__ uint32_t from_xor16(uint32_t x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+  return (uint32_t)r[0] ^ (uint32_t)r[1] ^ x;
+}
+__device__ __forceinline__ uint32_t from_xor32(uint32_t x) {
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return (uint32_t)r[0] ^ (uint32_t)r[1] ^ x;
 }
 
-// Maximum over the wave's 64 lanes, left on every lane: DPP within each 16-lane row
-// (quad swaps, half mirror, mirror: each a max with a DPP operand), then rows paired by
-// v_permlane16_swap and halves by v_permlane32_swap.
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
-  x = max_dpp<0xB1>(x);   // quad_perm [1,0,3,2]
-  x = max_dpp<0x4E>(x);   // quad_perm [2,3,0,1]
-  x = max_dpp<0x141>(x);  // row_half_mirror
-  x = max_dpp<0x140>(x);  // row_mirror
-  x = pair_max(__builtin_amdgcn_permlane16_swap(x, x, false, false));
-  return pair_max(__builtin_amdgcn_permlane32_swap(x, x, false, false));
+// x of lane l ^ MASK.
+template <int MASK>
+__device__ __forceinline__ uint32_t from_lane_xor(uint32_t x) {
+  if constexpr ((MASK & 32) != 0) x = from_xor32(x);
+  if constexpr ((MASK & 16) != 0) x = from_xor16(x);
+  constexpr int m = MASK & 15;
+  if constexpr (m == 1) return dpp<0xB1>(x);          // quad_perm [1,0,3,2]
+  if constexpr (m == 2) return dpp<0x4E>(x);          // quad_perm [2,3,0,1]
+  if constexpr (m == 3) return dpp<0x1B>(x);          // quad_perm [3,2,1,0]
+  if constexpr (m == 4) return dpp<0x1B>(dpp<0x141>(x));  // row_half_mirror (l ^ 7), then l ^ 3
+  if constexpr (m == 7) return dpp<0x141>(x);
+  if constexpr (m == 8) return dpp<0x128>(x);         // row_ror:8
+  if constexpr (m == 15) return dpp<0x140>(x);        // row_mirror
+  static_assert(m == 0 || m == 1 || m == 2 || m == 3 || m == 4 || m == 7 || m == 8 || m == 15, "lane mask");
+  return x;
 }
 
-// The largest 64-bit key of the wave, on every lane, in two 32-bit reductions: the
-// largest upper half (the saliency bits), then the largest lower half (~index) among
-// the lanes holding that upper half.
-__device__ __forceinline__ uint64_t wave_max_key(uint64_t k) {
-  const uint32_t hi = wave_max_u32((uint32_t)(k >> 32));
-  const uint32_t lo = wave_max_u32((uint32_t)(k >> 32) == hi ? (uint32_t)k : 0u);
-  return ((uint64_t)hi << 32) | lo;
+// One compare-exchange of a descending sort: of lanes l and l ^ MASK, the one whose bit BIT is
+// clear keeps the larger value.
+template <int MASK, int BIT>
+__device__ __forceinline__ uint32_t exchange(uint32_t x, int lane) {
+  const uint32_t y = from_lane_xor<MASK>(x);
+  return (lane & BIT) ? min(x, y) : max(x, y);
 }
 
-// Top-`budget` (budget <= kWaveTopK) of sal[0..N), ascending, into s_idx.  Wave w owns
-// tokens [w*Q, (w+1)*Q), lane l the tokens w*Q + l + 64 m (m < kLaneSlots), kept as
-// keys sorted in registers.  Each round the wave's best remaining key is found by a
-// wave-wide maximum and its lane drops it.  Wave 0 then extracts the top `budget` of
-// the 4 x budget winners the same way (two per lane) and orders them by index.
-constexpr int kWaveTopK = 32;
-static_assert(NW * kWaveTopK <= 128, "the final extraction holds two candidates per lane");
-constexpr int kLaneSlots = 8;  // tokens per lane: the wave path takes N <= 4 * 64 * 8
+// The wave's 64 values sorted, largest on lane 0 (bitonic; the first step of each merge pairs
+// mirrored lanes, so that every run descends).
+__device__ __forceinline__ uint32_t wave_sort(uint32_t x, int lane) {
+  x = exchange<1, 1>(x, lane);
+  x = exchange<3, 2>(x, lane);
+  x = exchange<1, 1>(x, lane);
+  x = exchange<7, 4>(x, lane);
+  x = exchange<2, 2>(x, lane);
+  x = exchange<1, 1>(x, lane);
+  x = exchange<15, 8>(x, lane);
+  x = exchange<4, 4>(x, lane);
+  x = exchange<2, 2>(x, lane);
+  x = exchange<1, 1>(x, lane);
+  x = exchange<31, 16>(x, lane);
+  x = exchange<8, 8>(x, lane);
+  x = exchange<4, 4>(x, lane);
+  x = exchange<2, 2>(x, lane);
+  x = exchange<1, 1>(x, lane);
+  x = exchange<63, 32>(x, lane);
+  x = exchange<16, 16>(x, lane);
+  x = exchange<8, 8>(x, lane);
+  x = exchange<4, 4>(x, lane);
+  x = exchange<2, 2>(x, lane);
+  return exchange<1, 1>(x, lane);
+}
 
-__device__ void select_small(const float* sal, int N, int budget, int32_t* s_idx, uint64_t* s_cand) {
+// Top-`budget` (budget <= kRankedBudget, budget < N <= kRankedTokens), ascending, into s_idx;
+// v[m] is the value of token tid + NT m.  The budget-th largest of the 256 threads' maxima is
+// no larger than the budget-th largest value, so the tokens at or above it hold the
+// selection: budget threads' tokens at most, without ties.  They are gathered (in any order:
+// the keys are distinct), each one's rank is the number of larger keys, and the place of a
+// winner is the number of winners with a lower index.  False, on every thread, if more than
+// `cap` tokens are at or above the bound (many equal values).
+// What bounds it is the chain of dependent steps, one wave per SIMD.  (Before: `budget`
+// rounds of wave-wide maxima in each wave and again over their winners, or, above 32, the
+// radix select.  The selection launch for 24 layers of 1041 tokens: 9.7 -> 5.9 us at budget
+// 10, 15.0 -> 10.4 at 52; one layer 8.4 -> 5.6; an empty launch takes 2.4.  Reading eight
+// keys a step in the counts: 6.6 and 12.1.)  The lines: kLaneSlots values in registers, and a
+// budget at which the counts still take less than the radix select (admission of 24 layers at
+// budget 128: 43.0 us against 44.9 by radix; the gain shrinks from 5 us at 52).
+constexpr int kRankedBudget = 128;
+constexpr int kLaneSlots = 8;
+constexpr int kRankedTokens = NT * kLaneSlots;
+
+__device__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, int32_t* s_idx, uint64_t* s_cand,
+                              int cap) {
+  __shared__ uint32_t s_sorted[NT];
+  __shared__ int32_t s_win[kRankedBudget];
+  __shared__ uint32_t s_bound;
+  __shared__ int s_count;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int Q = (N + NW - 1) / NW;
-  const int lo = min(N, wave * Q), hi = min(N, lo + Q);
-  uint64_t v[kLaneSlots];
+  uint32_t best = 0u;  // (threads without tokens rank last: budget < N)
 #pragma unroll
-  for (int m = 0; m < kLaneSlots; ++m) {
-    const int j = lo + lane + 64 * m;
-    v[m] = j < hi ? rank_key(sal[j], j) : 0;
-  }
-#pragma unroll
-  for (int i = 0; i < kLaneSlots - 1; ++i) {  // descending
-#pragma unroll
-    for (int m = 0; m < kLaneSlots - 1 - i; ++m) {
-      const uint64_t x = v[m], y = v[m + 1];
-      v[m] = x > y ? x : y;
-      v[m + 1] = x > y ? y : x;
-    }
-  }
-  for (int r = 0; r < budget; ++r) {
-    const uint64_t win = wave_max_key(v[0]);
-    if (lane == 0) s_cand[wave * budget + r] = win;
-    if (win != 0 && win == v[0]) {  // this lane owns the winner (keys are distinct)
-#pragma unroll
-      for (int m = 0; m < kLaneSlots - 1; ++m) v[m] = v[m + 1];
-      v[kLaneSlots - 1] = 0;
-    }
-  }
+  for (int m = 0; m < kLaneSlots; ++m)
+    if (tid + NT * m < N) best = max(best, __float_as_uint(v[m]));
+  const uint32_t x = wave_sort(best, lane);
+  s_sorted[tid] = x;
+  if (tid == 0) s_count = 0;
   __syncthreads();
-  if (wave == 0) {
-    // The overall top `budget` lie among the NW * budget winners: two per lane, sorted.
-    const int nc = NW * budget;
-    uint64_t c0 = lane < nc ? s_cand[lane] : 0, c1 = lane + 64 < nc ? s_cand[lane + 64] : 0;
-    if (c1 > c0) {
-      const uint64_t t = c0;
-      c0 = c1;
-      c1 = t;
-    }
-    uint32_t mine = 0;  // lane r: ~index of the r-th winner
-    for (int r = 0; r < budget; ++r) {
-      const uint64_t win = wave_max_key(c0);
-      if (lane == r) mine = (uint32_t)win;
-      if (win == c0) {  // (a real key: fewer than budget + 1 tokens never reach this path)
-        c0 = c1;
-        c1 = 0;
+  // Rank of x among all 256, equal values in the order of waves then lanes.
+  int rank = lane;
+#pragma unroll
+  for (int o = 1; o < NW; ++o) {
+    const int w = (wave + o) & (NW - 1);
+    // first position of wave w's descending list whose value is below x (w earlier: equal
+    // values come before), or not above x (w later)
+    const uint32_t limit = x - (w < wave ? 1u : 0u);  // values > limit come before; x = 0 wraps: none are below 0
+    int lo = 0;
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1)
+      if (s_sorted[w * 64 + lo + step - 1] > limit || (w < wave && x == 0u)) lo += step;
+    if (s_sorted[w * 64 + lo] > limit || (w < wave && x == 0u)) ++lo;
+    rank += lo;
+  }
+  if (rank == budget - 1) s_bound = x;
+  __syncthreads();
+  const uint32_t bound = s_bound;
+  int n = 0;
+#pragma unroll
+  for (int m = 0; m < kLaneSlots; ++m) n += tid + NT * m < N && __float_as_uint(v[m]) >= bound;
+  if (n > 0) {
+    int at = atomicAdd(&s_count, n);
+#pragma unroll
+    for (int m = 0; m < kLaneSlots; ++m)
+      if (tid + NT * m < N && __float_as_uint(v[m]) >= bound) {
+        if (at < cap) s_cand[at] = rank_key(v[m], tid + NT * m);
+        ++at;
       }
-    }
-    // lane r < budget: output slot = number of winners with a lower index
-    const uint32_t jr = ~mine;
-    int pos = 0;
-    for (int u = 0; u < budget; ++u) pos += ~(uint32_t)__builtin_amdgcn_readlane((int)mine, u) < jr;
-    if (lane < budget) s_idx[pos] = (int32_t)jr;
   }
   __syncthreads();
+  const int nc = s_count;
+  if (nc > cap) {  // uniform
+    __syncthreads();  // (s_cand is the caller's again)
+    return false;
+  }
+  for (int i = tid; i < nc; i += NT) {
+    const uint64_t key = s_cand[i];
+    int r = 0;
+    for (int u = 0; u < nc; ++u) r += s_cand[u] > key;
+    if (r < budget) s_win[r] = (int32_t)~(uint32_t)key;
+  }
+  __syncthreads();
+  if (tid < budget) {
+    const int32_t j = s_win[tid];
+    int pos = 0;
+    for (int u = 0; u < budget; ++u) pos += s_win[u] < j;
+    s_idx[pos] = j;
+  }
+  __syncthreads();
+  return true;
 }
 
 // Head-specific retention (the paper's rule, Sec. 3.3): one workgroup per (layer, head)
@@ -482,52 +537,63 @@ __device__ void select_small(const float* sal, int N, int budget, int32_t* s_idx
 // tokens to its own head.
 __global__ __launch_bounds__(NT) void select_kernel(AdmitArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ uint64_t s_cand[NW * kWaveTopK];
   const int H = a.n_heads, N = a.n_tokens, k = a.budget, tid = threadIdx.x;
   const int layer = blockIdx.x / H, h_own = blockIdx.x - layer * H;
   const AdmitLayer& L = a.layer[layer];
   float* s_sal = reinterpret_cast<float*>(smem);
   int32_t* s_idx = reinterpret_cast<int32_t*>(smem + (((size_t)N * 4 + 15) & ~(size_t)15));
 
-  if (a.shared_select) {
-    for (int j = tid; j < N; j += NT) {
-      float acc = 0.f;
-      for (int h = 0; h < H; ++h) acc += L.sal[(int64_t)h * N + j];
-      s_sal[j] = acc;
+  // The saliency that is ranked: the sum, in order, of n_rows rows of N values -- the head's
+  // row; its per-block rows (computed in the attention epilogue: the sum is the saliency,
+  // written out when asked for); or all heads' rows.  Tokens j0 + NT m, with kLaneSlots *
+  // kRowBatch loads in flight (token by token, eight rows at a time, the per-block rows of
+  // 1041 tokens took the launch 11.8 us instead of 7.4).
+  const int n_rows = a.shared_select ? H : a.sal_tiles > 0 ? a.sal_tiles : 1;
+  const float* const rows = a.shared_select ? L.sal : L.sal + (int64_t)h_own * n_rows * N;
+  auto values = [&](int j0, float (&acc)[kLaneSlots]) {
+    constexpr int M = kLaneSlots, kRowBatch = 4;
+#pragma unroll
+    for (int m = 0; m < M; ++m) acc[m] = 0.f;
+    for (int r0 = 0; r0 < n_rows; r0 += kRowBatch) {
+      float x[kRowBatch][M];
+#pragma unroll
+      for (int u = 0; u < kRowBatch; ++u)
+        if (r0 + u < n_rows)  // uniform
+#pragma unroll
+          for (int m = 0; m < M; ++m) x[u][m] = rows[(int64_t)(r0 + u) * N + min(j0 + NT * m, N - 1)];
+#pragma unroll
+      for (int u = 0; u < kRowBatch; ++u)
+        if (r0 + u < n_rows)
+#pragma unroll
+          for (int m = 0; m < M; ++m) acc[m] += x[u][m];
     }
-  } else if (a.sal_tiles > 0) {
-    // per-block saliency rows of this head (computed in the attention epilogue), summed
-    // in block order; the sum is the saliency, written out when asked for
-    // (eight rows' loads in flight per step)
-    const int T = a.sal_tiles;
-    const float* gs = L.sal + (int64_t)h_own * T * N;
-    for (int j = tid; j < N; j += NT) {
-      float acc = 0.f;
-      for (int t0 = 0; t0 < T; t0 += 8) {
-        float v[8];
+    if (a.sal_tiles > 0 && L.sal_out)
 #pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = t0 + u < T ? gs[(int64_t)(t0 + u) * N + j] : 0.f;
+      for (int m = 0; m < M; ++m)
+        if (j0 + NT * m < N) L.sal_out[(int64_t)h_own * N + j0 + NT * m] = acc[m];
+  };
+  if (k <= kRankedBudget && k < N && N <= kRankedTokens) {  // uniform
+    float v[kLaneSlots];
+    values(tid, v);
+    // (the candidates lie where the values would: N / 2 keys)
+    if (!select_ranked(v, N, k, s_idx, reinterpret_cast<uint64_t*>(s_sal), N / 2)) {
 #pragma unroll
-        for (int u = 0; u < 8; ++u)
-          if (t0 + u < T) acc = (t0 + u == 0) ? v[u] : acc + v[u];
-      }
-      s_sal[j] = acc;
-      if (L.sal_out) L.sal_out[(int64_t)h_own * N + j] = acc;
+      for (int m = 0; m < kLaneSlots; ++m)
+        if (tid + NT * m < N) s_sal[tid + NT * m] = v[m];
+      __syncthreads();
+      select_topk(s_sal, N, k, s_idx);
     }
   } else {
-    const float* gs = L.sal + (int64_t)h_own * N;
-    if ((N & 3) == 0) {
-      for (int j = tid; j < N / 4; j += NT)
-        reinterpret_cast<float4*>(s_sal)[j] = reinterpret_cast<const float4*>(gs)[j];
-    } else {
-      for (int j = tid; j < N; j += NT) s_sal[j] = gs[j];
+    for (int j0 = tid; j0 < N; j0 += NT * kLaneSlots) {
+      float v[kLaneSlots];
+      values(j0, v);
+#pragma unroll
+      for (int m = 0; m < kLaneSlots; ++m)
+        if (j0 + NT * m < N) s_sal[j0 + NT * m] = v[m];
     }
-  }
-  __syncthreads();
-  if (k <= kWaveTopK && k < N && N <= NW * 64 * kLaneSlots)
-    select_small(s_sal, N, k, s_idx, s_cand);
-  else
+    __syncthreads();
     select_topk(s_sal, N, k, s_idx);
+  }
   {
     const int h = h_own;
     if (L.idx)

@@ -1,0 +1,73 @@
+"""The selection's two ways (ranked candidates, radix select) at the edges where they
+change or could go wrong, against the oracle's stable sort."""
+import numpy as np
+import pytest
+
+import oracle
+from util import to_dev
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # (N, budget, values)
+    # fewer tokens than threads, one wave's worth, exactly 256 and one to either side
+    (2, 1, "spread"), (3, 2, "spread"), (63, 10, "spread"), (65, 32, "spread"), (255, 128, "spread"),
+    (256, 128, "spread"), (257, 127, "spread"),
+    # the largest ranked frame and budget, and one past each
+    (2048, 128, "spread"), (2048, 129, "spread"), (2049, 128, "spread"), (2047, 1, "spread"),
+    # all of the largest values on one thread, and on one wave
+    (1041, 5, "one thread"), (1041, 40, "one wave"), (1041, 64, "descending"), (1041, 64, "ascending"),
+    # ties: few levels (more candidates than fit: the radix way), half the tokens equal at
+    # the bound, all equal, all zero, zeros below a few values
+    (1041, 10, "levels"), (1041, 52, "half equal"), (1041, 10, "equal"), (200, 128, "zero"), (1041, 52, "few"),
+]
+
+
+def saliency(N, values, rng):
+    if values == "one thread":      # tokens t, t + 256, ... of one thread
+        s = rng.random(N) + 1.0
+        s[7::256] += 10.0
+    elif values == "one wave":      # threads 64 .. 127
+        s = rng.random(N) + 1.0 + 10.0 * ((np.arange(N) % 256) // 64 == 1)
+    elif values == "descending":
+        s = 2.0 - np.arange(N) / N
+    elif values == "ascending":
+        s = 1.0 + np.arange(N) / N
+    elif values == "levels":
+        s = rng.integers(1, 4, N).astype(np.float64)
+    elif values == "half equal":
+        s = np.where(rng.random(N) < 0.5, 1.0, rng.random(N))
+        s[rng.choice(N, 20, replace=False)] = 2.0 + rng.random(20)
+    elif values == "equal":
+        s = np.full(N, 0.25)
+    elif values == "zero":
+        s = np.zeros(N)
+    elif values == "few":
+        s = np.zeros(N)
+        s[rng.choice(N, 40, replace=False)] = 1.0
+    else:
+        s = rng.random(N)
+    return s.astype(np.float32)
+
+
+@pytest.mark.parametrize("N,budget,values", CASES)
+def test_selection_edges(N, budget, values):
+    import torch
+
+    from paper_2609_23286_amd import rv
+
+    print(f"selection N={N} budget={budget} {values}", flush=True)
+    H = 3
+    rng = np.random.default_rng(N * 1000 + budget)
+    sal = np.stack([saliency(N, values, rng) for _ in range(H)])
+    K, V = (rng.integers(0, 1 << 15, (N, H, 64)).astype(np.uint16) for _ in range(2))
+    mem = rv.Memory(H, reserve_tokens=budget)
+    idx = torch.full((H, budget), -7, dtype=torch.int32, device="cuda")
+    rv.admit(to_dev(sal), budget, to_dev(K), to_dev(V), mem, 42, idx)
+    ref = oracle.topk(sal.astype(np.float64), budget)
+    assert (idx.cpu().numpy() == ref).all()
+    mk, mv, prov = mem.read()
+    for h in range(H):
+        assert (mk[h].numpy().view(np.uint16) == K[ref[h], h]).all()
+        assert (mv[h].numpy().view(np.uint16) == V[ref[h], h]).all()
+        assert (prov[h, :, 1].numpy() == ref[h]).all()
+    mem.close()
