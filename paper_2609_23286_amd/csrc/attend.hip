@@ -564,7 +564,7 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(AttnArgs a) {
 //   blocks, then across the lane halves -- into tiles[h][qt][j].
 constexpr int kEpiGroups = 4;
 constexpr int kEpiQStride = kHeadDim + 8;   // staged query rows, 144 bytes
-constexpr int kEpiKeyBatch = 4;             // 32-key blocks whose K rows a wave loads together
+constexpr int kEpiKeyBatch = 3;             // 32-key blocks whose K rows a wave loads together
 
 // Final LSE (log2 units) of row `row` of a split unit, with merge_rows' arithmetic.
 __device__ float merged_lse2(const AttnArgs& a, int q, int ui, int row, int c_first, int c_last) {
@@ -589,7 +589,7 @@ __device__ float merged_lse2(const AttnArgs& a, int q, int ui, int row, int c_fi
   return mmax + __log2f(L);
 }
 
-__global__ __launch_bounds__(kAttnThreads) void attn_merge_sal_kernel(AttnArgs a, SalEpi e) {
+__global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArgs a, SalEpi e) {
   __shared__ float s_lse2[BQ];                        // by row
   __shared__ float s_lsec[BQ];                        // by sampled position (padding: +inf)
   __shared__ int s_list[BQ];
@@ -607,15 +607,6 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_sal_kernel(AttnArgs a
   const int c_first = chunk_holding(a, (int64_t)ui * a.U);
   const int c_last = chunk_holding(a, (int64_t)ui * a.U + a.T - 1);
 
-  // ---- this group's output rows, and the LSE of all the block's rows ----
-  if (c_first != c_last) merge_rows(a, q, unit, ui, g, c_first, c_last);
-  if (tid < BQ) {
-    const int qi = qt * BQ + tid;
-    float l2 = 0.f;
-    if (qi < N) l2 = c_first == c_last ? a.lse[(int64_t)h * N + qi] * kLog2e : merged_lse2(a, q, ui, tid, c_first, c_last);
-    s_lse2[tid] = l2;
-  }
-
   // ---- the block's sampled queries, in row order (waves 0 and 1 hold rows 0 .. 127) ----
   const int srow = wave * 64 + lane;
   bool sampled = false;
@@ -632,63 +623,106 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_sal_kernel(AttnArgs a
   __syncthreads();
   const int n_s = s_count[0] + s_count[1];
   const int ns_pad = (n_s + 31) & ~31;
+  const int l32 = lane & 31, half = lane >> 5;
   const uint16_t* Kh = e.K + (int64_t)h * e.kv_head;
   float* tile_h = e.tiles + ((int64_t)h * a.q_tiles + qt) * N;
   const int n_blocks = (N + 31) / 32;
   const int per_group = (n_blocks + kEpiGroups - 1) / kEpiGroups;
   const int blk0 = g * per_group, blk1 = min(n_blocks, blk0 + per_group);
+
+  constexpr int kWaves = kAttnThreads / 64;
+  // ---- everything the saliency reads, requested before the merge's partials: the key rows
+  // of the wave's first blocks and the sampled query rows (clamped, valid addresses) ----
+  bf16x8 kf[kEpiKeyBatch][4];
+  auto load_k = [&](int kb0) {
+#pragma unroll
+    for (int bb = 0; bb < kEpiKeyBatch; ++bb) {
+      const int j = min((kb0 + bb * kWaves) * 32 + l32, N - 1);  // past the range: result unused
+      const uint16_t* kp = Kh + (int64_t)j * e.kv_row + half * 8;
+#pragma unroll
+      for (int ds = 0; ds < 4; ++ds) kf[bb][ds] = *reinterpret_cast<const bf16x8*>(kp + ds * 16);
+    }
+  };
+  constexpr int kRowLoads = BQ * 8 / kAttnThreads;
+  uint4 qv[kRowLoads];
+  if (n_s > 0) {
+    load_k(blk0 + wave);
+#pragma unroll
+    for (int i = 0; i < kRowLoads; ++i) {
+      const int x = tid + i * kAttnThreads, row = s_list[min(x >> 3, n_s - 1)];
+      qv[i] = *reinterpret_cast<const uint4*>(a.Q + ((int64_t)(qt * BQ + row) * a.n_heads + h) * D + (x & 7) * 8);
+    }
+  }
+
+  // ---- this group's output rows, and the LSE of all the block's rows ----
+  if (c_first != c_last) merge_rows(a, q, unit, ui, g, c_first, c_last);
+  if (tid < BQ) {
+    const int qi = qt * BQ + tid;
+    float l2 = 0.f;
+    if (qi < N) l2 = c_first == c_last ? a.lse[(int64_t)h * N + qi] * kLog2e : merged_lse2(a, q, ui, tid, c_first, c_last);
+    s_lse2[tid] = l2;
+  }
   if (n_s == 0) {  // no sampled query in this block: its saliency row is the empty sum
     for (int j = blk0 * 32 + tid; j < min(N, blk1 * 32); j += kAttnThreads) tile_h[j] = 0.f;
     return;
   }
   // sampled query rows and their LSE (padding rows: zero rows, +inf -> weight 0)
-  for (int x = tid; x < ns_pad * 8; x += kAttnThreads) {
-    const int s = x >> 3, ch = x & 7;
-    uint4 v = make_uint4(0u, 0u, 0u, 0u);
-    if (s < n_s) v = *reinterpret_cast<const uint4*>(a.Q + ((int64_t)(qt * BQ + s_list[s]) * a.n_heads + h) * D + ch * 8);
-    *reinterpret_cast<uint4*>(&s_q[s * kEpiQStride + ch * 8]) = v;
+#pragma unroll
+  for (int i = 0; i < kRowLoads; ++i) {
+    const int x = tid + i * kAttnThreads, s = x >> 3;
+    if (s < ns_pad) *reinterpret_cast<uint4*>(&s_q[s * kEpiQStride + (x & 7) * 8]) = s < n_s ? qv[i] : uint4{0u, 0u, 0u, 0u};
   }
+  __syncthreads();
   for (int s = tid; s < ns_pad; s += kAttnThreads) s_lsec[s] = s < n_s ? s_lse2[s_list[s]] : __builtin_inff();
   __syncthreads();
 
-  // ---- this group's key blocks, kEpiKeyBatch per wave at a time ----
-  const int l32 = lane & 31, half = lane >> 5;
-  for (int kb0 = blk0 + wave; kb0 < blk1; kb0 += kEpiKeyBatch * (kAttnThreads / 64)) {
-    bf16x8 kf[kEpiKeyBatch][4];
-#pragma unroll
-    for (int bb = 0; bb < kEpiKeyBatch; ++bb) {
-      const int j = min((kb0 + bb * (kAttnThreads / 64)) * 32 + l32, N - 1);  // past the range: result unused
-      const uint16_t* kp = Kh + (int64_t)j * e.kv_row + half * 8;
-#pragma unroll
-      for (int ds = 0; ds < 4; ++ds) kf[bb][ds] = *reinterpret_cast<const bf16x8*>(kp + ds * 16);
-    }
-#pragma unroll
-    for (int bb = 0; bb < kEpiKeyBatch; ++bb) {
-      const int kb = kb0 + bb * (kAttnThreads / 64);
-      if (kb >= blk1) break;  // uniform
-      float acc = 0.f;
+  // ---- this group's key blocks, kEpiKeyBatch per wave at a time: each sampled query block's
+  // rows and LSE are read once for all of them, and their MFMA and exponential chains are
+  // independent ----
+  for (int kb0 = blk0 + wave; kb0 < blk1; kb0 += kEpiKeyBatch * kWaves) {
+    if (kb0 != blk0 + wave) load_k(kb0);
+    auto sweep = [&](auto nb_c) {
+      constexpr int NB = decltype(nb_c)::value;
+      float acc[NB] = {};
       for (int qb = 0; qb < ns_pad; qb += 32) {
         bf16x8 qf[4];
 #pragma unroll
         for (int ds = 0; ds < 4; ++ds)
           qf[ds] = *reinterpret_cast<const bf16x8*>(&s_q[(qb + l32) * kEpiQStride + ds * 16 + half * 8]);
-        f32x16 z = {};
-#pragma unroll
-        for (int ds = 0; ds < 4; ++ds) z = mfma32(qf[ds], kf[bb][ds], z);
         // accumulator entry r: sampled query qb + 8 (r / 4) + 4 half + r % 4, key kb * 32 + l32
-        float s0 = 0.f, s1 = 0.f;
+        float ls[16];
 #pragma unroll
-        for (int r = 0; r < 16; r += 2) {
-          const int i0 = qb + 8 * (r >> 2) + 4 * half + (r & 3);
-          s0 += __builtin_amdgcn_exp2f(fmaf(z[r], kScaleLog2, -s_lsec[i0]));
-          s1 += __builtin_amdgcn_exp2f(fmaf(z[r + 1], kScaleLog2, -s_lsec[i0 + 1]));
+        for (int r = 0; r < 16; ++r) ls[r] = s_lsec[qb + 8 * (r >> 2) + 4 * half + (r & 3)];
+        f32x16 z[NB] = {};
+#pragma unroll
+        for (int ds = 0; ds < 4; ++ds)
+#pragma unroll
+          for (int bb = 0; bb < NB; ++bb) z[bb] = mfma32(qf[ds], kf[bb][ds], z[bb]);
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) {
+          float s0 = 0.f, s1 = 0.f;
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            s0 += __builtin_amdgcn_exp2f(fmaf(z[bb][r], kScaleLog2, -ls[r]));
+            s1 += __builtin_amdgcn_exp2f(fmaf(z[bb][r + 1], kScaleLog2, -ls[r + 1]));
+          }
+          acc[bb] += s0 + s1;
         }
-        acc += s0 + s1;
       }
-      const float tot = acc + __shfl_xor(acc, 32);
-      const int j = kb * 32 + l32;
-      if (half == 0 && j < N) tile_h[j] = tot;
-    }
+#pragma unroll
+      for (int bb = 0; bb < NB; ++bb) {
+        const float tot = acc[bb] + __shfl_xor(acc[bb], 32);
+        const int j = (kb0 + bb * kWaves) * 32 + l32;
+        if (half == 0 && j < N) tile_h[j] = tot;
+      }
+    };
+    static_assert(kEpiKeyBatch == 3, "a batch holds one to three blocks");
+    if (kb0 + 2 * kWaves < blk1)  // uniform
+      sweep(std::integral_constant<int, 3>{});
+    else if (kb0 + kWaves < blk1)
+      sweep(std::integral_constant<int, 2>{});
+    else
+      sweep(std::integral_constant<int, 1>{});
   }
 }
 
