@@ -8,8 +8,8 @@
 // probability and no score matrix is stored.  A (layer, head) is split over
 // `sal_groups` workgroups of 4 wave64s (about three per CU over the launch), each taking
 // a contiguous range of 32-key blocks.  The sampled query rows and their LSE are staged
-// in LDS once per workgroup; each wave then takes its blocks two at a time (K rows in
-// registers) and sweeps the sampled queries in blocks of 32 with
+// in LDS once per workgroup; each wave then takes its blocks two at a time, or its only one (K
+// rows in registers) and sweeps the sampled queries in blocks of 32 with
 // v_mfma_f32_32x32x16_bf16 (Z = Q~ K^T, each lane owning one key column), each block's
 // accumulator seeded with -8 LSE of its rows so that the MFMAs leave 8 (z - LSE).  The
 // exponentials are summed in fp32 in a fixed order -- pairwise in-lane, over query
@@ -39,7 +39,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int D = kHeadDim;
 constexpr int NT = kAdmitThreads;  // 256
 constexpr int NW = NT / 64;
-constexpr int kBlocksPerStep = 2;  // 32-key blocks a saliency wave holds at once
+constexpr int kBlocksPerStep = 2;  // 32-key blocks a saliency wave holds at once (or 1: sal_kernel)
 static_assert(kBlocksPerStep == 2, "a range's last step holds one block or two");
 constexpr int QS_STRIDE = kSalQStride;  // staged sampled-query rows, 144 bytes
 constexpr int kPrefetchQBlock = 4;  // query block of a step at which the next step's K rows are requested
@@ -53,7 +53,7 @@ static_assert(NT == 256, "the radix histogram has one bin per thread");
 
 // The two query-row sources are separate instantiations, so that neither path's
 // memory waits are merged into the other's loop.
-template <bool kStaged>
+template <bool kStaged, int kStep>
 __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem) {
   const int H = a.n_heads, N = a.n_tokens, tid = threadIdx.x;
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -107,9 +107,9 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
   // K rows (B operands, K^T) of a step's blocks: lane's key, dims ds*16 + half*8 ..;
   // a pass's first step's rows are requested after its staging, each next step's rows
   // while the current step computes.
-  auto load_k = [&](int bb, bf16x8 (&kf)[kBlocksPerStep][4]) {
+  auto load_k = [&](int bb, bf16x8 (&kf)[kStep][4]) {
 #pragma unroll
-    for (int b = 0; b < kBlocksPerStep; ++b) {
+    for (int b = 0; b < kStep; ++b) {
       const int j = min((bb + b) * 32 + l32, N - 1);  // past the frame or the range: result unused
       const uint16_t* kp = Kh + (int64_t)j * kv_row + half * 8;
 #pragma unroll
@@ -147,8 +147,13 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
       if (c < rows * 8) *reinterpret_cast<uint4*>(&s_q[(c >> 3) * QS_STRIDE + ch * 8]) = v[u];
     }
   };
-  bf16x8 kf[kBlocksPerStep][4], kn[kBlocksPerStep][4];
-  for (int i0 = 0; i0 < nq_pad; i0 += NT * 4) {
+  bf16x8 kf[kStep][4], kn[kStep][4];
+  // With one block a step the first LSE values are stored once the first batch of rows is in
+  // flight too (one round trip less; with two there are no registers for it).
+  constexpr bool kLateLse = kStaged && kStep == 1;
+  float lse0[4];
+  if (kLateLse) lse_load(0, lse0);
+  for (int i0 = kLateLse ? NT * 4 : 0; i0 < nq_pad; i0 += NT * 4) {
     float lv[4];
     lse_load(i0, lv);
     lse_store(i0, lv);
@@ -163,20 +168,21 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
       for (int c0 = 0; c0 < rows * 8; c0 += NT * kStageBatch) {
         uint4 qv[kStageBatch];
         rows_load(p0, c0, qv);
+        if (kLateLse && p0 + c0 == 0) lse_store(0, lse0);
         rows_store(rows, c0, qv);
       }
     }
-    load_k(blk0 + wave * kBlocksPerStep, kf);  // (a wave without blocks loads rows it never uses)
+    load_k(blk0 + wave * kStep, kf);  // (a wave without blocks loads rows it never uses)
     __syncthreads();
 
-    for (int bb = blk0 + wave * kBlocksPerStep; bb < blk1; bb += NW * kBlocksPerStep) {
+    for (int bb = blk0 + wave * kStep; bb < blk1; bb += NW * kStep) {
       // The next step's K rows are requested a few query blocks into this step, not at
       // its start: every workgroup of the launch stages at once, and the workgroups
       // served first would otherwise queue their next step's rows ahead of the staging
       // loads of those served last.
-      const bool prefetch = bb + NW * kBlocksPerStep < blk1;
+      const bool prefetch = bb + NW * kStep < blk1;
       const int q_prefetch = p0 + 32 * min(kPrefetchQBlock, (p1 - p0) / 32 - 1);
-      // NB blocks held (the range's last step may hold fewer than kBlocksPerStep).
+      // NB blocks held (the range's last step may hold fewer than kStep).
       auto sweep = [&](auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
         float acc[NB] = {};
@@ -195,7 +201,7 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
         bf16x8 qf[4];
         load_q(p0, qf);
         for (int qb = p0; qb < p1; qb += 32) {
-          if (prefetch && qb == q_prefetch) load_k(bb + NW * kBlocksPerStep, kn);
+          if (prefetch && qb == q_prefetch) load_k(bb + NW * kStep, kn);
           // Wave priority 0 for the MFMAs, 1 from the next block's row reads through the
           // exponentials: of the waves sharing a SIMD, those in their vector work issue
           // first, so the MFMAs of the others run under it (about -2 % per launch against a
@@ -248,12 +254,12 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
           }
         }
       };
-      if (bb + kBlocksPerStep <= blk1)  // uniform
-        sweep(std::integral_constant<int, kBlocksPerStep>{});
-      else
+      if (bb + kStep <= blk1)  // uniform
+        sweep(std::integral_constant<int, kStep>{});
+      else if (kStep > 1)
         sweep(std::integral_constant<int, 1>{});
 #pragma unroll
-      for (int b = 0; b < kBlocksPerStep; ++b)
+      for (int b = 0; b < kStep; ++b)
 #pragma unroll
         for (int ds = 0; ds < 4; ++ds) kf[b][ds] = kn[b][ds];
     }
@@ -261,12 +267,18 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
   }
 }
 
+// kStep: blocks a wave takes at a time.  Two, or one where no range holds more than a block a
+// wave (launches of few layers: the wave's chain of query blocks is what the launch waits for,
+// and half as long with one).  Saliency and selection back to back, two -> one: one layer of
+// 1041 tokens 14.5 -> 12.3 us, 4 layers 16.5 -> 15.6, two layers with every patch sampled 33.3
+// -> 26.8.  (One instantiation for both made the launch of 24 layers 0.9 % longer.)
+template <int kStep>
 __global__ __launch_bounds__(NT, 3) void sal_kernel(AdmitArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (a.stage_queries)
-    sal_body<true>(a, smem);
+    sal_body<true, kStep>(a, smem);
   else
-    sal_body<false>(a, smem);
+    sal_body<false, kStep>(a, smem);
 }
 
 // ---- selection and append -----------------------------------------------------------
@@ -651,15 +663,19 @@ hipError_t set_lds_limit(const void* kernel, int* cached, int limit) {
 }  // namespace
 
 hipError_t launch_admit(const AdmitArgs& a, int max_lds, hipStream_t s) {
-  static int sal_attr = 0, sel_attr = 0;
+  static int sal_attr = 0, sal1_attr = 0, sel_attr = 0;
   const int limit = admit_max_dynamic_lds(max_lds);
   if (a.mode & kModeSaliency) {
-    hipError_t e = set_lds_limit((const void*)sal_kernel, &sal_attr, limit);
+    int b0, b1;
+    sal_group_blocks(a, 0, (a.n_tokens + 31) / 32, &b0, &b1);  // (no later group holds more)
+    const bool one = b1 - b0 <= NW;
+    auto* const kernel = one ? sal_kernel<1> : sal_kernel<kBlocksPerStep>;
+    hipError_t e = set_lds_limit((const void*)kernel, one ? &sal1_attr : &sal_attr, limit);
     if (e != hipSuccess) return e;
     const unsigned X = (unsigned)(a.sal_xcds > 0 ? a.sal_xcds : 1);
     const unsigned n_lh = (unsigned)(a.n_layers * a.n_heads);
     const unsigned grid = (n_lh + X - 1) / X * X * (unsigned)a.sal_groups;
-    hipLaunchKernelGGL(sal_kernel, dim3(grid), dim3(NT), sal_lds_bytes(a), s, a);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(NT), sal_lds_bytes(a), s, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -182,13 +182,18 @@ size_t admit_lds_bytes(const AdmitArgs& a) {
 int admit_max_dynamic_lds(int max_lds) { return max_lds - kAdmitStaticLdsMargin; }
 
 void plan_saliency(AdmitArgs* a, int n_lh, int n_cus, int max_lds) {
-  // About three 4-wave workgroups per CU over the launch, and at least one 32-key
-  // block per wave.
+  // About three 4-wave workgroups per CU over the launch, each wave taking blocks two at a
+  // time; or one block a wave, where the launch then still fits four workgroups per CU (124
+  // registers a wave instead of 167).  7 layers of 1041 tokens, saliency and selection: 18.9 us
+  // with one block a wave (1008 workgroups), 23.2 with up to two (784); every patch sampled:
+  // 47.6 and 62.1.  Beyond that the launch would take a second round of workgroups, each
+  // staging the query rows again.
   constexpr int kWaves = kAdmitThreads / 64;
   const int n_blocks = (a->n_tokens + 31) / 32;
-  const int max_groups = n_blocks / kWaves > 1 ? n_blocks / kWaves : 1;
-  int g = (3 * n_cus + n_lh - 1) / (n_lh > 0 ? n_lh : 1);
-  a->sal_groups = g < 1 ? 1 : (g > max_groups ? max_groups : g);
+  const int max_groups = (n_blocks + kWaves - 1) / kWaves;
+  const int g = (3 * n_cus + n_lh - 1) / (n_lh > 0 ? n_lh : 1);
+  const bool one = (int64_t)n_lh * max_groups <= (int64_t)4 * n_cus;
+  a->sal_groups = one || g > max_groups ? max_groups : g < 1 ? 1 : g;
   // Sampled query rows are staged in passes of q_pass rows, sized so that three
   // workgroups fit a CU's LDS; the pass size depends only on n_q and the device, so
   // every launch of the same frame shape sums in the same order.  An empty subset has

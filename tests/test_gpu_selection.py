@@ -71,3 +71,42 @@ def test_selection_edges(N, budget, values):
         assert (mv[h].numpy().view(np.uint16) == V[ref[h], h]).all()
         assert (prov[h, :, 1].numpy() == ref[h]).all()
     mem.close()
+
+
+@pytest.mark.parametrize("grid,special,stride,layers", [
+    ((28, 37), 5, 2, 24),   # one block a wave alone, two in 24 layers
+    ((28, 37), 5, 1, 8),    # several passes of staged query rows; 8 layers: past the line
+    ((28, 37), 5, 2, 7),    # 7 layers: the last shape with one block a wave
+    ((12, 11), 1, 3, 24),   # 5 blocks: ranges of 4 and 1
+    ((8, 8), 0, 2, 24),     # 2 blocks for 4 waves
+])
+def test_saliency_bits_do_not_depend_on_the_launch(grid, special, stride, layers):
+    """One layer alone and among others, whose launch splits the keys otherwise: the same
+    saliency bits and selection, within 1e-3 of the oracle's saliency."""
+    import torch
+
+    from paper_2609_23286_amd import rv, synth
+
+    rv.init()
+    N, H, k = grid[0] * grid[1] + special, 16, 5
+    qs = (*grid, special, stride)
+    print(f"saliency N={N} stride={stride} layers={layers}", flush=True)
+    Q, K, V = (synth.normal_bf16(77, 0, 0, tag, (N, H, 64), 0.125) for tag in range(3))
+    dev = [to_dev(x) for x in (Q, K, V)]
+    lse = torch.logsumexp(torch.einsum("ihd,jhd->hij", *(x.view(torch.bfloat16).float().cpu() for x in dev[:2])) / 8, 2)
+    lse = lse.cuda().contiguous()
+    got = []
+    for L in (1, layers):
+        mems = [rv.Memory(H, reserve_tokens=k) for _ in range(L)]
+        sal = [torch.empty((H, N), device="cuda") for _ in range(L)]
+        idx = [torch.empty((H, k), dtype=torch.int32, device="cuda") for _ in range(L)]
+        rv.admit_layers(*([x] * L for x in dev), [lse] * L, qs, k, mems, 0, sal, idx)
+        torch.cuda.synchronize()
+        got += list(zip(sal, idx))
+        for m in mems:
+            m.close()
+    for s, i in got[1:]:
+        assert torch.equal(s, got[0][0]) and torch.equal(i, got[0][1])
+    z = torch.einsum("ihd,jhd->hij", *(x.view(torch.bfloat16).double().cpu() for x in dev[:2])) / 8
+    want = torch.exp(z - lse.cpu().double()[:, :, None])[:, oracle.qsub_index(*qs)].sum(1)
+    assert ((got[0][0].cpu().double() - want).abs() <= 1e-3 * want).all()
