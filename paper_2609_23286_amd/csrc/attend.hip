@@ -562,6 +562,10 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(AttnArgs a) {
 //   LSE log2(e)) over the sampled queries with v_mfma_f32_32x32x16_bf16 (Z = Q~ K^T, one
 //   lane per key), in a fixed order -- in-lane over the accumulator rows, over 32-query
 //   blocks, then across the lane halves -- into tiles[h][qt][j].
+// What bounds it is latency: the merge's round trips (4.8 us alone), then each wave's chain of
+// (key block, query block) steps.  So the key and query rows are requested ahead of the
+// merge's partials and the wave's two or three key blocks go through each query block
+// together: 11.7 -> 10.8 us a launch (1041 tokens, 16 heads, 3,210 rows remembered).
 constexpr int kEpiGroups = 4;
 constexpr int kEpiQStride = kHeadDim + 8;   // staged query rows, 144 bytes
 constexpr int kEpiKeyBatch = 3;             // 32-key blocks whose K rows a wave loads together
