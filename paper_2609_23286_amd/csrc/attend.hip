@@ -492,6 +492,501 @@ __device__ void process_segment(const AttnArgs& a, int q, int c, int unit, int u
   __syncthreads();  // (the ring is the next segment's)
 }
 
+// ---- long chunks --------------------------------------------------------------------
+//
+// The forward launch where a workgroup has many tiles (plan_long_chunks).  The same units,
+// chunks, tiles and partial results; another split of a workgroup's work over its waves.
+// Wave (wq, kh) takes queries 64 wq .. + 63 of the unit as two 32-query blocks and keys 32 kh
+// .. + 31 of every tile, so that each K and V fragment read from LDS serves two blocks (half
+// the LDS reads: 5.5 M instead of 10.5 M wave instructions at 52,000 rows), and the work is
+// pipelined by half a tile: the score MFMAs of the next block and the value MFMAs of the one
+// before run under each block's exponentials.  The two key halves meet in LDS at a segment's
+// end.
+//
+// What bounds it is the card's power: it runs at about 2.05 GHz with data like the streams'
+// and at 2.4 GHz with zeros.  Against attn_fwd_kernel the launch takes 10 % fewer cycles and
+// 3-8 % less time where a chunk holds 90 tiles or more (1041 tokens, 16 heads: 20,000 rows
+// 107-109 -> 104-106 us, 52,000 rows 249-259 -> 243-246; 1374 tokens: 20,000 rows 138 -> 131,
+// 52,000 rows 338 -> 309), the same at 40 to 60, and up to 2.5 us more below: the longer
+// prologue, the exchange at the end and odd tiles (1041 tokens, empty memory: 15.3 -> 17.5).
+constexpr float kRefFloor = -1.7e29f;   // lowest softmax reference: above kNegBig * kScaleLog2
+
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t x = reinterpret_cast<uint64_t>(p);
+  const uint32_t lo = (uint32_t)uniform((int)(uint32_t)x), hi = (uint32_t)uniform((int)(uint32_t)(x >> 32));
+  return reinterpret_cast<const char*>((uint64_t)hi << 32 | lo);
+}
+
+template <int P>
+using Slot = std::integral_constant<int, P>;
+
+// As TileCursor, with the byte offsets formed from the thread's row and the tile's row stride.
+struct LongCursor {
+  const char* km;          // memory K / V rows of this head
+  const char* vm;
+  const char* kc;          // the frame's K / V rows of this head
+  const char* vc;
+  uint32_t cur_row;        // bytes between consecutive frame rows: H * 64 * 2
+  uint32_t r, g0, g1;      // this thread's row (and row + 32), and byte offsets in the rows
+  int nt_mem;              // memory tiles
+  int t_last;              // index of the unit's last tile
+  int mem_tail;            // valid rows of the last memory tile
+  int tok_tail;            // valid rows of the last frame tile
+};
+
+__device__ __forceinline__ int long_tile_valid(const LongCursor& tc, int t) {
+  int v = BK;
+  if (t == tc.t_last) v = tc.tok_tail;
+  if (t == tc.nt_mem - 1) v = tc.mem_tail;
+  return v;
+}
+
+// Lane l's 16 bytes at base + off go to LDS byte lds + 16 l.  (Assembly: the compiler would
+// wait for every such load in flight before the transposing LDS reads, whichever slots they
+// read; the pipeline below waits for them itself, at the end of a step.  No register is
+// written.  The wait states are those a scalar that a vector instruction wrote needs before a
+// load reads it: the compiler does not look for such hazards here.)
+__device__ __forceinline__ void lds_load16_asm(const char* base, uint32_t off, uint32_t lds) {
+  asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(off), "s"(base), "{m0}"(lds));
+}
+
+// Global addresses of tile t: the K and V bases and this thread's byte offsets of its two
+// 16-byte pieces (selects, no branches: they are computed in the middle of a tile's MFMAs).
+struct LongSrc {
+  const char *k, *v;
+  uint32_t o0, o1;
+};
+__device__ __forceinline__ LongSrc long_src(const LongCursor& tc, int t) {
+  const bool mem = t < tc.nt_mem;  // uniform
+  const uint32_t row = mem ? D * 2 : tc.cur_row;
+  const int64_t at = (int64_t)(mem ? t : t - tc.nt_mem) * BK * row;
+  const uint32_t last = (uint32_t)long_tile_valid(tc, t) - 1;
+  LongSrc ts;
+  ts.k = uniform_ptr((mem ? tc.km : tc.kc) + at);
+  ts.v = uniform_ptr((mem ? tc.vm : tc.vc) + at);
+  ts.o0 = min(tc.r, last) * row + tc.g0;
+  ts.o1 = min(tc.r + 32, last) * row + tc.g1;
+  return ts;
+}
+
+// Issue one tile's loads into an LDS slot (completion: vmcnt + barrier).  `slot` is the byte
+// address of the tile plus this wave's row block (rows 8w .. 8w+7; the second load fills rows
+// 32 + 8w ..).
+__device__ __forceinline__ void load_rows(const char* base, const LongSrc& ts, uint32_t slot) {
+  lds_load16_asm(base, ts.o0, slot);
+  lds_load16_asm(base, ts.o1, slot + 32 * D * 2);
+}
+
+// One 32-query block of a wave: its softmax state over the wave's keys.
+struct QueryBlock {
+  float m;      // reference of the exponentials (z * log2(e) / 8)
+  float l;      // this lane's share of the row sum
+  f32x16 o0;    // O^T rows d = 0..31 for this lane's query (accumulator layout)
+  f32x16 o1;    // d = 32..63
+};
+
+// Scores of keys >= valid (of the wave's 32) become -1e30: sat(key + 1 - valid) is 1 exactly
+// for them, 0 otherwise (arithmetic masking keeps 16 lane masks out of scalar registers).
+// Accumulator entry r of a lane is key 8*(r/4) + 4*half + r%4.
+__device__ __forceinline__ void mask_keys(f32x16& s, int half, int valid) {
+  const float fv = (float)(valid - 4 * half - 1);
+#pragma unroll
+  for (int r = 0; r < 16; ++r) s[r] = fmaf(__saturatef((float)(8 * (r >> 2) + (r & 3)) - fv), kNegBig, s[r]);
+}
+
+// Maximum of the 32 keys' scaled scores of each query, at least kRefFloor (a wave whose 32
+// keys are all masked then gets p = 0 for each, not 2^(rounding error of -1e30)).
+__device__ __forceinline__ float tile_ref(const f32x16& s) {
+  float mx = s[0];
+#pragma unroll
+  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
+  return fmaxf(half_max(mx) * kScaleLog2, kRefFloor);
+}
+
+// p = 2^(z log2(e) / 8 - m) of one query block's 32 keys, as the value product's operand;
+// returns this lane's share of their sum.
+__device__ __forceinline__ float exponentials(const f32x16& s, float m, bf16x8 (&p)[2]) {
+  float rsum = -0.f;  // -0 + x == x: the first add folds away
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    const float e0 = __builtin_amdgcn_exp2f(fmaf(s[r], kScaleLog2, -m));
+    const float e1 = __builtin_amdgcn_exp2f(fmaf(s[r + 1], kScaleLog2, -m));
+    rsum += e0 + e1;
+    p[r >> 3][r & 7] = (__bf16)e0;
+    p[r >> 3][(r & 7) + 1] = (__bf16)e1;
+  }
+  return rsum;
+}
+
+// The end of a block's softmax: adds the row sum, or, where some lane's sum reaches 2^64 (or
+// inf), takes the exact path -- raise the reference to the keys' maximum, rescale the
+// accumulators, recompute p.  Terms far below the reference underflow to 0, exactly as they
+// would relative to the true maximum, so nothing else depends on the reference.
+__device__ __forceinline__ void add_row_sum(const f32x16& s, QueryBlock& b, bf16x8 (&p)[2], float rsum) {
+  asm volatile("" : "+v"(p[0]), "+v"(p[1]));  // (p is formed before the branch, among the MFMAs)
+  if (__builtin_expect(__any(!(rsum < kOverflowGuard)), 0)) {
+    const float m_new = fmaxf(b.m, tile_ref(s));
+    const float alpha = __builtin_amdgcn_exp2f(b.m - m_new);
+    b.l *= alpha;
+    b.o0 *= alpha;
+    b.o1 *= alpha;
+    b.m = m_new;
+    rsum = exponentials(s, m_new, p);
+  }
+  b.l += rsum;
+}
+
+// Key tiles t0..t1-1 of `unit` (queue-local index ui) as part of chunk c of queue q.
+__device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, int c, int unit, int ui, int t0,
+                                                     int t1, uint16_t* lds) {
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = uniform(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  unit = uniform(unit);
+  t0 = uniform(t0);
+  t1 = uniform(t1);
+  const int h = uniform(unit / a.q_tiles), qt = uniform(unit % a.q_tiles);
+  const int q0 = qt * BQ + wave * 32;
+  const int qi = q0 + l32;
+  const bool wave_active = q0 < a.n_tokens;
+
+  LongCursor tc;
+  {
+    tc.km = reinterpret_cast<const char*>(a.memK + (int64_t)h * a.head_stride * D);
+    tc.vm = reinterpret_cast<const char*>(a.memV + (int64_t)h * a.head_stride * D);
+    tc.kc = reinterpret_cast<const char*>(a.K + (int64_t)h * D);
+    tc.vc = reinterpret_cast<const char*>(a.V + (int64_t)h * D);
+    tc.cur_row = 2u * (uint32_t)(a.n_heads * D);
+    tc.r = tid >> 3;
+    tc.g0 = 16u * ((tid & 7) ^ sw(tid >> 3));
+    tc.g1 = 16u * ((tid & 7) ^ sw((tid >> 3) + 32));
+    tc.nt_mem = a.nt_mem;
+    tc.t_last = a.T - 1;
+    tc.mem_tail = a.nt_mem > 0 ? (int)(a.mem_len - (int64_t)(a.nt_mem - 1) * BK) : BK;
+    tc.tok_tail = a.T > a.nt_mem ? a.n_fkeys - (a.T - 1 - a.nt_mem) * BK : BK;
+  }
+  // Wave (wq, kh): query blocks 64 wq + 0..31 and + 32..63 of the unit, and keys 32 kh ..
+  // + 31 of every tile.
+  const int wq = wave >> 1, kh = wave & 1;
+  const bool computes = qt * BQ + 64 * wq < a.n_tokens;
+
+  // B operand of S^T = K Q^T: this lane's two queries, head dims ds*16 + half*8 .. +7.
+  bf16x8 qf[2][4];
+#pragma unroll
+  for (int qb = 0; qb < 2; ++qb) {
+    const int qr = min(qt * BQ + 64 * wq + 32 * qb + l32, a.n_tokens - 1);
+    const uint16_t* qp = a.Q + ((int64_t)qr * a.n_heads + h) * D + half * 8;
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) qf[qb][ds] = *reinterpret_cast<const bf16x8*>(qp + ds * 16);
+  }
+  QueryBlock b0, b1;
+  b0.l = b1.l = 0.f;
+  b0.o0 = b0.o1 = b1.o0 = b1.o1 = f32x16{};
+
+  constexpr uint32_t kSlot = TILE * 2, kVRing = 4 * kSlot;
+  // This lane's byte offsets in a tile.  K (A operand of S^T): row 32 kh + l32, chunk
+  // 2 ds + half.  V^T operand through transposing LDS reads: within each 16-lane group, lane
+  // i receives element i%4 of the 8-byte chunk addressed by lane 4r + i/4 (r = 0..3), so lane
+  // 4r + j points at row (key) r, columns d0 + 4j .. +3: lane i then holds V[key r][d0 + i]
+  // for the 4 keys.  Keys follow the P^T slot order: for k-step ks and lane half hh, slots
+  // 0..3 are keys ks*16 + 4hh + r, slots 4..7 keys ks*16 + 8 + 4hh + r.
+  uint32_t ko[4], vo[2][2];   // byte offsets in the ring, of the half the next step reads
+  {
+    const int g = lane >> 4, i16 = lane & 15, rr = i16 >> 2, jj = i16 & 3;
+    const int col = 16 * (g & 1) + 4 * jj;
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) ko[ds] = 2 * swz(32 * kh + l32, 2 * ds + half);
+#pragma unroll
+    for (int hi = 0; hi < 2; ++hi)
+#pragma unroll
+      for (int db = 0; db < 2; ++db)
+        vo[hi][db] = 2 * (swz(32 * kh + 8 * hi + 4 * (g >> 1) + rr, (db * 32 + col) >> 3) + (col & 7));
+  }
+  bf16x8 kf[4], vf[2][2];
+  f32x16 s0, s1;
+  bf16x8 p0[2], p1[2];
+  typedef __attribute__((address_space(3))) const char lds_char;
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  lds_char* const ldsb = (lds_char*)(lds_void*)lds;
+  auto read_k = [&](int slot) {
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) kf[ds] = *(lds_bf16x8*)(ldsb + ko[ds] + slot * kSlot);
+  };
+  auto read_v = [&](int slot) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int db = 0; db < 2; ++db) {
+        const int at = kVRing + slot * kSlot + ks * 16 * D * 2;
+        const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(ldsb + vo[0][db] + at));
+        const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(ldsb + vo[1][db] + at));
+        vf[ks][db] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+      }
+  };
+  auto scores = [&](const bf16x8 (&q)[4], f32x16& s) {
+    s = f32x16{};
+#pragma unroll
+    for (int ds = 0; ds < 4; ++ds) s = mfma32(kf[ds], q[ds], s);
+  };
+  auto values = [&](const bf16x8 (&p)[2], QueryBlock& b) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      b.o0 = mfma32(vf[ks][0], p[ks], b.o0);
+      b.o1 = mfma32(vf[ks][1], p[ks], b.o1);
+    }
+  };
+
+  // Ring of four K and four V slots (K slots, then V slots); slot s + half's offset.
+  const uint32_t ring = (uint32_t)(uintptr_t)(lds_void*)lds + wave * 8 * D * 2;
+  auto flip = [&](auto& off) {  // to the other half of the ring
+#pragma unroll
+    for (auto& x : off) x ^= 2 * kSlot;
+  };
+  auto tile = [&](int t, auto k_next, auto v_this, auto load_a, auto load_b) {
+    const int valid = long_tile_valid(tc, t) - 32 * kh;
+    load_a();
+    if (__builtin_expect(valid < 32, 0)) mask_keys(s0, half, valid);
+    {
+      scores(qf[1], s1);
+      const float r0 = exponentials(s0, b0.m, p0);
+      read_k(decltype(k_next)::value);
+      values(p1, b1);
+      add_row_sum(s0, b0, p0, r0);
+    }
+    load_b();
+    if (__builtin_expect(valid < 32, 0)) mask_keys(s1, half, valid);
+    {
+      read_v(decltype(v_this)::value);
+      scores(qf[0], s0);
+      const float r1 = exponentials(s1, b1.m, p1);
+      values(p0, b0);
+      add_row_sum(s1, b1, p1, r1);
+    }
+  };
+  // Running addresses of the loads of a step at t: K tile t + 3 and V tile t + 2 of the part
+  // (memory or frame) that tile t + 2 lies in, whose tiles before run_end are full.
+  const char *k3, *v2;
+  uint32_t step_bytes;
+  LongSrc off;
+  int run_end;
+  bool part_mem;
+  auto set_part = [&](bool mem, int t) {
+    part_mem = mem;
+    const uint32_t row = mem ? D * 2 : tc.cur_row;
+    step_bytes = BK * row;
+    const int64_t i = t + 2 - (mem ? 0 : tc.nt_mem);
+    k3 = uniform_ptr((mem ? tc.km : tc.kc) + (i + 1) * step_bytes);
+    v2 = uniform_ptr((mem ? tc.vm : tc.vc) + i * step_bytes);
+    off.o0 = tc.r * row + tc.g0;
+    off.o1 = (tc.r + 32) * row + tc.g1;
+    const int full = mem ? tc.nt_mem - (tc.mem_tail < BK) : tc.t_last + 1 - (tc.tok_tail < BK);
+    run_end = uniform(min(full, t1));
+  };
+  // A step computes tiles t, t + 1, in ring half y (byte offset 0 or 2 kSlot; z: the other): K
+  // and V tiles t, t + 1 lie in its two slots.  The K fragments are read one tile early, so the
+  // loads of the next pair that go out in a step are K t + 3, t + 4 and V t + 2, t + 3, into
+  // the slots freed at the last barrier.  Full tiles of one part go by running addresses,
+  // others by long_src.
+  uint32_t y = 0;
+  auto loads_a = [&](int t, bool run) {
+    const uint32_t z = 2 * kSlot - y;
+    if (run) {
+      load_rows(v2, off, ring + kVRing + z);
+      load_rows(k3, off, ring + z + kSlot);
+    } else {
+      if (t + 2 < t1) {
+        const LongSrc x = long_src(tc, t + 2);
+        load_rows(x.v, x, ring + kVRing + z);
+      }
+      if (t + 3 < t1) {
+        const LongSrc x = long_src(tc, t + 3);
+        load_rows(x.k, x, ring + z + kSlot);
+      }
+    }
+  };
+  auto loads_b = [&](int t, bool run) {
+    const uint32_t z = 2 * kSlot - y;
+    if (run) {
+      load_rows(v2 + step_bytes, off, ring + kVRing + z + kSlot);
+      load_rows(k3 + step_bytes, off, ring + y);
+    } else {
+      if (t + 3 < t1) {
+        const LongSrc x = long_src(tc, t + 3);
+        load_rows(x.v, x, ring + kVRing + z + kSlot);
+      }
+      if (t + 4 < t1) {
+        const LongSrc x = long_src(tc, t + 4);
+        load_rows(x.k, x, ring + y);
+      }
+    }
+    k3 += 2 * step_bytes;
+    v2 += 2 * step_bytes;
+  };
+  auto end_step = [&]() {
+    y = 2 * kSlot - y;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  };
+  {
+    const LongSrc x0 = long_src(tc, t0);
+    load_rows(x0.k, x0, ring);
+    load_rows(x0.v, x0, ring + kVRing);
+    if (t0 + 1 < t1) {
+      const LongSrc x1 = long_src(tc, t0 + 1);
+      load_rows(x1.k, x1, ring + kSlot);
+      load_rows(x1.v, x1, ring + kVRing + kSlot);
+    }
+    if (t0 + 2 < t1) {
+      const LongSrc x2 = long_src(tc, t0 + 2);
+      load_rows(x2.k, x2, ring + 2 * kSlot);
+    }
+  }
+  // (the query fragments pass through: the compiler's own wait for them belongs here, not in
+  // the loop, where it would be a wait for the tiles in flight)
+  asm volatile("s_waitcnt vmcnt(0)"
+               : "+v"(qf[0][0]), "+v"(qf[0][1]), "+v"(qf[0][2]), "+v"(qf[0][3]), "+v"(qf[1][0]), "+v"(qf[1][1]),
+                 "+v"(qf[1][2]), "+v"(qf[1][3])::"memory");
+  __syncthreads();
+  if (computes) {
+    // The first tile's maxima are the references; its second block's scores are formed again
+    // in the pipeline, and the pipeline's first value product multiplies zeros.
+    const int valid = long_tile_valid(tc, t0) - 32 * kh;
+    read_k(0);
+    scores(qf[1], s1);
+    scores(qf[0], s0);
+    if (valid < 32) mask_keys(s1, half, valid);
+    b1.m = tile_ref(s1);
+    f32x16 sm = s0;
+    if (valid < 32) mask_keys(sm, half, valid);
+    b0.m = tile_ref(sm);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      p1[i] = bf16x8{};
+      vf[i][0] = vf[i][1] = bf16x8{};
+    }
+  }
+  set_part(t0 + 2 < tc.nt_mem, t0);
+  if (computes) {
+    for (int t = t0; t < t1; t = uniform(t + 2)) {
+      if (part_mem && t + 2 >= tc.nt_mem) set_part(false, t);
+      const bool run = t + 4 < run_end;
+      tile(t, Slot<1>{}, Slot<0>{}, [&] { loads_a(t, run); }, [&] { loads_b(t, run); });
+      flip(ko);
+      if (t + 1 < t1) tile(t + 1, Slot<0>{}, Slot<1>{}, [] {}, [] {});
+      flip(vo[0]);
+      flip(vo[1]);
+      end_step();
+    }
+    values(p1, b1);
+  } else {  // a wave without queries only loads
+    for (int t = t0; t < t1; t = uniform(t + 2)) {
+      loads_a(t, false);
+      loads_b(t, false);
+      end_step();
+    }
+  }
+
+  // Each wave keeps one of its query blocks (block kh: rows 32 wave .. + 31 of the unit), takes
+  // the other key half's sums of it from the wave beside it, and hands over the other block.
+  float l_tot, m_tot;
+  f32x16 o0, o1;
+  {
+    const bool hi = kh != 0;
+    f32x16 g0, g1;  // handed over
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      g0[r] = hi ? b0.o0[r] : b1.o0[r];
+      g1[r] = hi ? b0.o1[r] : b1.o1[r];
+      o0[r] = hi ? b1.o0[r] : b0.o0[r];
+      o1[r] = hi ? b1.o1[r] : b0.o1[r];
+    }
+    const float mg = hi ? b0.m : b1.m, lg = half_sum(hi ? b0.l : b1.l);
+    const float mk = hi ? b1.m : b0.m, lk = half_sum(hi ? b1.l : b0.l);
+    static_assert(TILE * 2 == 8 * 64 * 16, "a wave's 32 accumulator entries fill one K slot");
+    float* const xs = reinterpret_cast<float*>(lds + 4 * TILE);  // [wave][2][64 lanes]
+    if (computes) {
+      float4* po = reinterpret_cast<float4*>(lds + wave * TILE) + lane;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        po[j * 64] = make_float4(g0[4 * j], g0[4 * j + 1], g0[4 * j + 2], g0[4 * j + 3]);
+        po[(4 + j) * 64] = make_float4(g1[4 * j], g1[4 * j + 1], g1[4 * j + 2], g1[4 * j + 3]);
+      }
+      xs[wave * 128 + lane] = mg;
+      xs[wave * 128 + 64 + lane] = lg;
+    }
+    __syncthreads();
+    if (computes) {
+      const int w = wave ^ 1;
+      const float mo = xs[w * 128 + lane], lo = xs[w * 128 + 64 + lane];
+      m_tot = fmaxf(mk, mo);
+      const float ak = __builtin_amdgcn_exp2f(mk - m_tot), ao = __builtin_amdgcn_exp2f(mo - m_tot);
+      l_tot = lk * ak + lo * ao;
+      const float4* po = reinterpret_cast<const float4*>(lds + w * TILE) + lane;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float4 x = po[j * 64], y = po[(4 + j) * 64];
+        const float xv[4] = {x.x, x.y, x.z, x.w}, yv[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          o0[4 * j + i] = fmaf(xv[i], ao, o0[4 * j + i] * ak);
+          o1[4 * j + i] = fmaf(yv[i], ao, o1[4 * j + i] * ak);
+        }
+      }
+    }
+    __syncthreads();
+  }
+  // The output rows (normalised by the row sum, bf16) go out through LDS: each wave stages
+  // its 32 rows, then writes whole 128-byte rows, as process_segment does.
+  constexpr int kOutStageRow = D + 8;
+  static_assert(32 * kOutStageRow <= TILE, "a wave's rows fit one V slot");
+  uint16_t* const st = lds + (4 + wave) * TILE;
+  if (wave_active) {
+    const float inv = 1.f / l_tot;
+    uint16_t* sp = st + l32 * kOutStageRow + 4 * half;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      *reinterpret_cast<uint2*>(sp + 8 * j) =
+          to_bf16x4(o0[4 * j] * inv, o0[4 * j + 1] * inv, o0[4 * j + 2] * inv, o0[4 * j + 3] * inv);
+      *reinterpret_cast<uint2*>(sp + 32 + 8 * j) =
+          to_bf16x4(o1[4 * j] * inv, o1[4 * j + 1] * inv, o1[4 * j + 2] * inv, o1[4 * j + 3] * inv);
+    }
+  }
+  __syncthreads();
+  const int r8 = lane >> 3, c8 = (lane & 7) * 8;
+  if (t0 == 0 && t1 == a.T) {
+    // the whole unit in this chunk: final output rows and LSE
+    if (wave_active) {
+      if (half == 0 && qi < a.n_tokens) a.lse[(int64_t)h * a.n_tokens + qi] = (m_tot + __log2f(l_tot)) * kLn2;
+#pragma unroll
+      for (int pass = 0; pass < 4; ++pass) {
+        const int r = pass * 8 + r8, qr = q0 + r;
+        if (qr < a.n_tokens)
+          *reinterpret_cast<uint4*>(a.out + ((int64_t)qr * a.n_heads + h) * D + c8) =
+              *reinterpret_cast<const uint4*>(st + r * kOutStageRow + c8);
+      }
+    }
+  } else {
+    // partial result, merged by the second launch: the normalised output rows in bf16
+    // (the merge weights them by 2^(m - M) l), then m and l in fp32
+    const int seg = chunk_start(a, c) >= (int64_t)ui * a.U ? 0 : 1;
+    float* ps = a.part + (int64_t)(2 * (a.chunk_base[q] + c) + seg) * kAttnSlotFloats;
+    if (wave_active) {
+      if (half == 0) {
+        const int row = wave * 32 + l32;
+        ps[kSlotStatsFloat + row] = m_tot;
+        ps[kSlotStatsFloat + BQ + row] = l_tot;
+      }
+      uint16_t* po = reinterpret_cast<uint16_t*>(ps) + wave * 32 * D;
+#pragma unroll
+      for (int pass = 0; pass < 4; ++pass) {
+        const int r = pass * 8 + r8;
+        *reinterpret_cast<uint4*>(po + r * D + c8) = *reinterpret_cast<const uint4*>(st + r * kOutStageRow + c8);
+      }
+    }
+  }
+  __syncthreads();  // (the ring is the next segment's)
+}
+
 // Requests a field from every 64-byte line of the argument block at once: the reads that
 // follow (some of them through indices that other arguments give) then hit the scalar
 // cache, instead of each line's first read costing a round trip of its own.
@@ -528,6 +1023,30 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWgPerCu) void attn_fwd_kernel(At
     }
     const int seg_end = min(it_end, ui * a.U + a.T);
     process_segment(a, q, c, ub + ui, ui, t0, t0 + (seg_end - it), lds);
+    it = (seg_end == ui * a.U + a.T) ? (ui + 1) * a.U : seg_end;
+  }
+}
+
+__global__ __launch_bounds__(kAttnThreads, kAttnWgPerCu) void attn_long_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t lds[8 * TILE];
+  touch_args(a);
+  const int q = (int)(blockIdx.x % (unsigned)a.n_queues);
+  const int c = (int)(blockIdx.x / (unsigned)a.n_queues);
+  if (c >= a.n_chunks[q]) return;
+  const int ub = a.unit_base[q];
+  int64_t first, end;
+  chunk_iters(a, c, (int64_t)(a.unit_base[q + 1] - ub) * a.U, &first, &end);
+  int it = (int)first;
+  const int it_end = (int)end;
+  while (it < it_end) {
+    const int ui = it / a.U;
+    const int t0 = it - ui * a.U;
+    if (t0 >= a.T) {  // padding after the unit's last tile (split mode)
+      it = (ui + 1) * a.U;
+      continue;
+    }
+    const int seg_end = min(it_end, ui * a.U + a.T);
+    process_long_segment(a, q, c, ub + ui, ui, t0, t0 + (seg_end - it), lds);
     it = (seg_end == ui * a.U + a.T) ? (ui + 1) * a.U : seg_end;
   }
 }
@@ -746,9 +1265,15 @@ hipError_t static_scratch_address(float** ptr) {
   return hipGetSymbolAddress(reinterpret_cast<void**>(ptr), HIP_SYMBOL(scratch));
 }
 
-hipError_t launch_attention(const AttnArgs& a, int grid, bool merge, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_kernel, dim3(grid), dim3(kAttnThreads), 0, s, a);
-  hipError_t e = hipGetLastError();
+namespace {
+hipError_t launch_forward(const AttnArgs& a, int grid, bool long_chunks, hipStream_t s) {
+  hipLaunchKernelGGL(long_chunks ? attn_long_kernel : attn_fwd_kernel, dim3(grid), dim3(kAttnThreads), 0, s, a);
+  return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_attention(const AttnArgs& a, int grid, bool merge, bool long_chunks, hipStream_t s) {
+  hipError_t e = launch_forward(a, grid, long_chunks, s);
   if (e != hipSuccess || !merge) return e;
   int max_units = 0;
   for (int q = 0; q < a.n_queues; ++q) max_units = max(max_units, a.unit_base[q + 1] - a.unit_base[q]);
@@ -757,9 +1282,9 @@ hipError_t launch_attention(const AttnArgs& a, int grid, bool merge, hipStream_t
   return hipGetLastError();
 }
 
-hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(attn_fwd_kernel, dim3(grid), dim3(kAttnThreads), 0, s, a);
-  hipError_t err = hipGetLastError();
+hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, bool long_chunks,
+                                     hipStream_t s) {
+  hipError_t err = launch_forward(a, grid, long_chunks, s);
   if (err != hipSuccess) return err;
   int max_units = 0;
   for (int q = 0; q < a.n_queues; ++q) max_units = max(max_units, a.unit_base[q + 1] - a.unit_base[q]);

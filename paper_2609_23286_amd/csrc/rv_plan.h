@@ -201,6 +201,15 @@ AttnPlan plan_attention(int n_cus, int n_queues, int n_tokens, int n_fkeys, int6
 // Whether some unit's key range is split over several chunks (then a merge launch runs).
 bool plan_splits_units(const AttnPlan& p);
 
+// Whether the plan's chunks hold so many tiles on average that the forward kernel for long
+// chunks is the faster one.  Measured against the other (1041 and 1374 tokens, 16, 8 and 4
+// heads; 500 tokens, 16 heads): +1 to +3 % at 30-50 tiles a chunk, 0 to -8 % at 58, -2 to -5 %
+// at 90-116, -5 to -8 % at 230-300.
+constexpr int kLongChunkTiles = 88;
+inline bool plan_long_chunks(const AttnPlan& p) {
+  return (int64_t)p.n_units * p.T >= (int64_t)kLongChunkTiles * p.total_chunks;
+}
+
 // Partial slots a plan writes into: two per chunk (a chunk's segment of the unit it starts
 // in, and of the unit it ends in).
 inline int64_t plan_partial_slots(const AttnPlan& p) { return 2 * (int64_t)p.total_chunks; }

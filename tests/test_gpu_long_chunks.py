@@ -1,0 +1,74 @@
+"""The forward kernel for long chunks (64 queries by 32 keys a wave, key halves merged in
+LDS) against the oracle, at the edges of its tiles and segments.  RV_ATTN_* overrides make
+chunks long enough with little work; each case checks that its plan is one the kernel takes."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2609_23286_amd import synth
+from util import LSE_ATOL, OUT_ATOL, bf16_to_f64, out_error_bound, to_dev, to_host_u16
+
+pytestmark = pytest.mark.gpu
+
+LONG_CHUNK_TILES = 88
+
+CASES = [  # (N, H, M, split, minimum chunk, per cent of a first chunk, keys)
+    # one chunk a unit; query counts around the 32- and 64-query blocks, memory tails in the
+    # first key half, at its end, in the second, and none
+    (1, 1, 5633, "1", "1", "140", "flat"), (31, 2, 5652, "1", "1", "140", "flat"),
+    (32, 1, 5664, "1", "1", "140", "flat"), (33, 2, 5665, "1", "1", "140", "flat"),
+    (64, 3, 5695, "1", "1", "140", "flat"), (65, 2, 5696, "1", "1", "140", "flat"),
+    (97, 1, 5700, "1", "1", "140", "flat"), (128, 2, 5632, "1", "1", "140", "flat"),
+    (300, 2, 5555, "1", "1", "140", "flat"),
+    # a frame without memory, and two and three pieces a unit
+    (5700, 1, 0, "1", "1", "140", "flat"), (129, 2, 11300, "2", "1", "140", "flat"),
+    (160, 1, 17000, "3", "1", "140", "flat"),
+    # stream-K chunks of 98 tiles over units of 99: segments of 1 to 8 tiles at the units' ends,
+    # the shortest of them the frame's last tile alone, with one key
+    (129, 32, 6100, "0", "98", "100", "flat"),
+    # logits that grow along the keys (the reference is raised again and again), that fall, and
+    # a few units' worth of spread
+    (130, 2, 5700, "1", "1", "140", "rising"), (130, 2, 5700, "1", "1", "140", "falling"),
+    (70, 2, 5700, "1", "1", "140", "spread"),
+]
+
+
+@pytest.mark.parametrize("N,H,M,split,min_chunk,first_pct,keys", CASES)
+def test_long_chunks_match_oracle(N, H, M, split, min_chunk, first_pct, keys, monkeypatch):
+    import torch
+
+    from paper_2609_23286_amd import rv
+
+    print(f"long chunks N={N} H={H} M={M} split={split} keys={keys}", flush=True)
+    rv.init()
+    monkeypatch.setenv("RV_ATTN_SPLIT", split)
+    monkeypatch.setenv("RV_ATTN_MIN_CHUNK", min_chunk)
+    monkeypatch.setenv("RV_ATTN_FIRST_PCT", first_pct)
+    p = rv.attention_plan(N, N, M, H, 256, 8)
+    assert p.n_units * p.T >= LONG_CHUNK_TILES * p.total_chunks
+    rv.reserve_workspace(N, H, M)
+    sigma = 0.125 if keys == "flat" else 1.0
+    Q, K, V = (synth.normal_bf16(31 + N, 0, 0, tag, (N, H, 64), sigma) for tag in range(3))
+    memK, memV = (synth.normal_bf16(32 + N, 1, 0, tag, (H, M, 64), sigma) for tag in (synth.TAG_MEMK, synth.TAG_MEMV))
+    if keys in ("rising", "falling"):   # logits of standard deviation 0.05 .. 12
+        ramp = np.linspace(0.05, 12.0, M)[:: 1 if keys == "rising" else -1]
+        memK = synth.f32_to_bf16_bits((bf16_to_f64(memK) * ramp[None, :, None]).astype(np.float32))
+    mem = rv.Memory(H, reserve_tokens=M + 5)
+    if M:
+        mem.write(torch.from_numpy(memK.view(np.int16)), torch.from_numpy(memV.view(np.int16)))
+    out = torch.empty((N, H, 64), dtype=torch.int16, device="cuda")
+    lse = torch.empty((H, N), dtype=torch.float32, device="cuda")
+    rv.attend_frame(to_dev(Q), to_dev(K), to_dev(V), mem, out, lse)
+    rv.device_status()
+    mem.close()
+    got, got_lse = bf16_to_f64(to_host_u16(out)), lse.cpu().numpy().astype(np.float64)
+    want, want_lse = oracle.attend(Q, K, V, memK, memV, M)
+    vmax = max(np.abs(bf16_to_f64(V)).max(), np.abs(bf16_to_f64(memV)).max() if M else 0.0)
+    # The logits are fp32 sums of 64 products: an error of up to about 64 2^-24 of the largest
+    # one, relative, moves the LSE by as much and every weight by that factor.
+    z_err = 64 * 2.0 ** -24 * np.abs(want_lse).max()
+    assert np.isfinite(got).all() and np.isfinite(got_lse).all()
+    assert np.abs(got - want).max() <= out_error_bound(want, vmax) + 2 * z_err * vmax
+    if keys == "flat":
+        assert np.abs(got - want).max() <= OUT_ATOL
+    assert np.abs(got_lse - want_lse).max() <= LSE_ATOL + z_err
