@@ -39,7 +39,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 constexpr int D = kHeadDim;
 constexpr int NT = kAdmitThreads;  // 256
 constexpr int NW = NT / 64;
-constexpr int kBlocksPerStep = 2;  // 32-key blocks a saliency wave holds at once (or 1: sal_kernel)
+constexpr int kBlocksPerStep = 2;  // 32-key blocks a saliency wave holds at once (sal_one_kernel: 1)
 static_assert(kBlocksPerStep == 2, "a range's last step holds one block or two");
 constexpr int QS_STRIDE = kSalQStride;  // staged sampled-query rows, 144 bytes
 constexpr int kPrefetchQBlock = 4;  // query block of a step at which the next step's K rows are requested
@@ -267,18 +267,25 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
   }
 }
 
-// kStep: blocks a wave takes at a time.  Two, or one where no range holds more than a block a
-// wave (launches of few layers: the wave's chain of query blocks is what the launch waits for,
+// Blocks a wave takes at a time: two, or one (sal_one_kernel) where no range holds more than a
+// block a wave (launches of few layers: the wave's chain of query blocks is what the launch waits for,
 // and half as long with one).  Saliency and selection back to back, two -> one: one layer of
 // 1041 tokens 14.5 -> 12.3 us, 4 layers 16.5 -> 15.6, two layers with every patch sampled 33.3
 // -> 26.8.  (One instantiation for both made the launch of 24 layers 0.9 % longer.)
-template <int kStep>
 __global__ __launch_bounds__(NT, 3) void sal_kernel(AdmitArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (a.stage_queries)
-    sal_body<true, kStep>(a, smem);
+    sal_body<true, kBlocksPerStep>(a, smem);
   else
-    sal_body<false, kStep>(a, smem);
+    sal_body<false, kBlocksPerStep>(a, smem);
+}
+
+__global__ __launch_bounds__(NT, 3) void sal_one_kernel(AdmitArgs a) {
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  if (a.stage_queries)
+    sal_body<true, 1>(a, smem);
+  else
+    sal_body<false, 1>(a, smem);
 }
 
 // ---- selection and append -----------------------------------------------------------
@@ -663,14 +670,15 @@ hipError_t set_lds_limit(const void* kernel, int* cached, int limit) {
 }  // namespace
 
 hipError_t launch_admit(const AdmitArgs& a, int max_lds, hipStream_t s) {
-  static int sal_attr = 0, sal1_attr = 0, sel_attr = 0;
+  static int sal_attr = 0, sal_one_attr = 0, sel_attr = 0;
   const int limit = admit_max_dynamic_lds(max_lds);
   if (a.mode & kModeSaliency) {
     int b0, b1;
     sal_group_blocks(a, 0, (a.n_tokens + 31) / 32, &b0, &b1);  // (no later group holds more)
     const bool one = b1 - b0 <= NW;
-    auto* const kernel = one ? sal_kernel<1> : sal_kernel<kBlocksPerStep>;
-    hipError_t e = set_lds_limit((const void*)kernel, one ? &sal1_attr : &sal_attr, limit);
+    auto* const kernel = one ? sal_one_kernel : sal_kernel;
+    hipError_t e = set_lds_limit((const void*)sal_kernel, &sal_attr, limit);
+    if (e == hipSuccess) e = set_lds_limit((const void*)sal_one_kernel, &sal_one_attr, limit);
     if (e != hipSuccess) return e;
     const unsigned X = (unsigned)(a.sal_xcds > 0 ? a.sal_xcds : 1);
     const unsigned n_lh = (unsigned)(a.n_layers * a.n_heads);
