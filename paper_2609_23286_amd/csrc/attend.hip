@@ -636,15 +636,37 @@ __device__ __forceinline__ void add_row_sum(const f32x16& s, QueryBlock& b, bf16
   b.l += rsum;
 }
 
-// Key tiles t0..t1-1 of `unit` (queue-local index ui) as part of chunk c of queue q.
+// The tile a segment starts at, `done` iterations into chunk c.  The chunks of a head cover
+// different key ranges, but the sums over a segment's keys take any order: with chunks of E
+// tiles, the chunk that has worked for i iterations takes the tile that is i modulo E where its
+// segment holds one, so that a head's chunks are at the same few tiles at a time (one for each E
+// tiles of the context) and find them in their XCD's L2.  In key order the chunks of plans that
+// are not aligned with the units drift apart and fetch the keys from beyond L2 once for each
+// query tile (700 tokens, 16 heads: 30,000 rows 113 -> 104 us, 52,000 rows 188 -> 167; 1041
+// tokens, 12 heads, 52,000 rows 202 -> 192; aligned plans within 1 %).
+__device__ __forceinline__ int first_tile(const AttnArgs& a, int c, int done, int t0, int t1) {
+  const int E = (c < a.n_first ? a.E : a.E1) / kCutScale;
+  if (E <= 1) return t0;
+  const int ahead = (done - t0) % E;
+  const int ts = t0 + (ahead < 0 ? ahead + E : ahead);
+  return ts < t1 ? ts : t0;
+}
+
+// Key tiles t0..t1-1 of `unit` (queue-local index ui) as part of chunk c of queue q, in the
+// order ts..t1-1, t0..ts-1.
 __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, int c, int unit, int ui, int t0,
-                                                     int t1, uint16_t* lds) {
+                                                     int t1, int ts, uint16_t* lds) {
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = uniform(tid >> 6);
   const int l32 = lane & 31, half = lane >> 5;
   unit = uniform(unit);
   t0 = uniform(t0);
   t1 = uniform(t1);
+  ts = uniform(ts);
+  const int n = t1 - t0;              // tiles, taken in the order of index 0 .. n - 1
+  const int n_up = t1 - ts;           // indices before the order wraps to t0
+  const int wrap = n_up < n ? n : 0;  // subtracted from ts + i for i >= n_up
+  auto tile_at = [&](int i) { return ts + i - (i >= n_up ? wrap : 0); };
   const int h = uniform(unit / a.q_tiles), qt = uniform(unit % a.q_tiles);
   const int q0 = qt * BQ + wave * 32;
   const int qi = q0 + l32;
@@ -743,7 +765,7 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
     for (auto& x : off) x ^= 2 * kSlot;
   };
   auto tile = [&](int t, auto k_next, auto v_this, auto load_a, auto load_b) {
-    const int valid = long_tile_valid(tc, t) - 32 * kh;
+    const int valid = long_tile_valid(tc, tile_at(t)) - 32 * kh;
     load_a();
     if (__builtin_expect(valid < 32, 0)) mask_keys(s0, half, valid);
     {
@@ -763,26 +785,27 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
       add_row_sum(s1, b1, p1, r1);
     }
   };
-  // Running addresses of the loads of a step at t: K tile t + 3 and V tile t + 2 of the part
-  // (memory or frame) that tile t + 2 lies in, whose tiles before run_end are full.
-  const char *k3, *v2;
-  uint32_t step_bytes;
-  LongSrc off;
-  int run_end;
-  bool part_mem;
-  auto set_part = [&](bool mem, int t) {
-    part_mem = mem;
+  // Running addresses of the loads of a step at index t: K of index t + 3 and V of t + 2, while
+  // those tiles and that of t + 4 follow one another in one part (memory or frame) and are full
+  // (t + 4 < run_end).
+  const char *k3 = tc.km, *v2 = tc.vm;
+  uint32_t step_bytes = 0;
+  LongSrc off{};
+  int run_end = 0;
+  auto set_run = [&](int t) {
+    const int at = tile_at(t + 2);
+    const bool mem = at < tc.nt_mem;
     const uint32_t row = mem ? D * 2 : tc.cur_row;
     step_bytes = BK * row;
-    const int64_t i = t + 2 - (mem ? 0 : tc.nt_mem);
+    const int64_t i = at - (mem ? 0 : tc.nt_mem);
     k3 = uniform_ptr((mem ? tc.km : tc.kc) + (i + 1) * step_bytes);
     v2 = uniform_ptr((mem ? tc.vm : tc.vc) + i * step_bytes);
     off.o0 = tc.r * row + tc.g0;
     off.o1 = (tc.r + 32) * row + tc.g1;
     const int full = mem ? tc.nt_mem - (tc.mem_tail < BK) : tc.t_last + 1 - (tc.tok_tail < BK);
-    run_end = uniform(min(full, t1));
+    run_end = uniform(t + 2 + min(full - at, (t + 2 < n_up ? n_up : n) - (t + 2)));
   };
-  // A step computes tiles t, t + 1, in ring half y (byte offset 0 or 2 kSlot; z: the other): K
+  // A step computes indices t, t + 1, in ring half y (byte offset 0 or 2 kSlot; z: the other): K
   // and V tiles t, t + 1 lie in its two slots.  The K fragments are read one tile early, so the
   // loads of the next pair that go out in a step are K t + 3, t + 4 and V t + 2, t + 3, into
   // the slots freed at the last barrier.  Full tiles of one part go by running addresses,
@@ -794,12 +817,12 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
       load_rows(v2, off, ring + kVRing + z);
       load_rows(k3, off, ring + z + kSlot);
     } else {
-      if (t + 2 < t1) {
-        const LongSrc x = long_src(tc, t + 2);
+      if (t + 2 < n) {
+        const LongSrc x = long_src(tc, tile_at(t + 2));
         load_rows(x.v, x, ring + kVRing + z);
       }
-      if (t + 3 < t1) {
-        const LongSrc x = long_src(tc, t + 3);
+      if (t + 3 < n) {
+        const LongSrc x = long_src(tc, tile_at(t + 3));
         load_rows(x.k, x, ring + z + kSlot);
       }
     }
@@ -810,12 +833,12 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
       load_rows(v2 + step_bytes, off, ring + kVRing + z + kSlot);
       load_rows(k3 + step_bytes, off, ring + y);
     } else {
-      if (t + 3 < t1) {
-        const LongSrc x = long_src(tc, t + 3);
+      if (t + 3 < n) {
+        const LongSrc x = long_src(tc, tile_at(t + 3));
         load_rows(x.v, x, ring + kVRing + z + kSlot);
       }
-      if (t + 4 < t1) {
-        const LongSrc x = long_src(tc, t + 4);
+      if (t + 4 < n) {
+        const LongSrc x = long_src(tc, tile_at(t + 4));
         load_rows(x.k, x, ring + y);
       }
     }
@@ -828,16 +851,16 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
     __syncthreads();
   };
   {
-    const LongSrc x0 = long_src(tc, t0);
+    const LongSrc x0 = long_src(tc, ts);
     load_rows(x0.k, x0, ring);
     load_rows(x0.v, x0, ring + kVRing);
-    if (t0 + 1 < t1) {
-      const LongSrc x1 = long_src(tc, t0 + 1);
+    if (n > 1) {
+      const LongSrc x1 = long_src(tc, tile_at(1));
       load_rows(x1.k, x1, ring + kSlot);
       load_rows(x1.v, x1, ring + kVRing + kSlot);
     }
-    if (t0 + 2 < t1) {
-      const LongSrc x2 = long_src(tc, t0 + 2);
+    if (n > 2) {
+      const LongSrc x2 = long_src(tc, tile_at(2));
       load_rows(x2.k, x2, ring + 2 * kSlot);
     }
   }
@@ -850,7 +873,7 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
   if (computes) {
     // The first tile's maxima are the references; its second block's scores are formed again
     // in the pipeline, and the pipeline's first value product multiplies zeros.
-    const int valid = long_tile_valid(tc, t0) - 32 * kh;
+    const int valid = long_tile_valid(tc, ts) - 32 * kh;
     read_k(0);
     scores(qf[1], s1);
     scores(qf[0], s0);
@@ -865,21 +888,20 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
       vf[i][0] = vf[i][1] = bf16x8{};
     }
   }
-  set_part(t0 + 2 < tc.nt_mem, t0);
   if (computes) {
-    for (int t = t0; t < t1; t = uniform(t + 2)) {
-      if (part_mem && t + 2 >= tc.nt_mem) set_part(false, t);
+    for (int t = 0; t < n; t = uniform(t + 2)) {
+      if (t + 2 >= run_end && t + 2 < n) set_run(t);
       const bool run = t + 4 < run_end;
       tile(t, Slot<1>{}, Slot<0>{}, [&] { loads_a(t, run); }, [&] { loads_b(t, run); });
       flip(ko);
-      if (t + 1 < t1) tile(t + 1, Slot<0>{}, Slot<1>{}, [] {}, [] {});
+      if (t + 1 < n) tile(t + 1, Slot<0>{}, Slot<1>{}, [] {}, [] {});
       flip(vo[0]);
       flip(vo[1]);
       end_step();
     }
     values(p1, b1);
   } else {  // a wave without queries only loads
-    for (int t = t0; t < t1; t = uniform(t + 2)) {
+    for (int t = 0; t < n; t = uniform(t + 2)) {
       loads_a(t, false);
       loads_b(t, false);
       end_step();
@@ -1046,7 +1068,8 @@ __global__ __launch_bounds__(kAttnThreads, kAttnWgPerCu) void attn_long_kernel(A
       continue;
     }
     const int seg_end = min(it_end, ui * a.U + a.T);
-    process_long_segment(a, q, c, ub + ui, ui, t0, t0 + (seg_end - it), lds);
+    const int t1 = t0 + (seg_end - it);
+    process_long_segment(a, q, c, ub + ui, ui, t0, t1, first_tile(a, c, it - (int)first, t0, t1), lds);
     it = (seg_end == ui * a.U + a.T) ? (ui + 1) * a.U : seg_end;
   }
 }
