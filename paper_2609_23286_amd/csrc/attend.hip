@@ -517,9 +517,6 @@ __device__ __forceinline__ const char* uniform_ptr(const char* p) {
   return reinterpret_cast<const char*>((uint64_t)hi << 32 | lo);
 }
 
-template <int P>
-using Slot = std::integral_constant<int, P>;
-
 // As TileCursor, with the byte offsets formed from the thread's row and the tile's row stride.
 struct LongCursor {
   const char* km;          // memory K / V rows of this head
@@ -758,33 +755,13 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
     }
   };
 
-  // Ring of four K and four V slots (K slots, then V slots); slot s + half's offset.
+  // The ring: four K slots, then four V slots; `ring` is K slot 0 plus this wave's row block.
   const uint32_t ring = (uint32_t)(uintptr_t)(lds_void*)lds + wave * 8 * D * 2;
   auto flip = [&](auto& off) {  // to the other half of the ring
 #pragma unroll
     for (auto& x : off) x ^= 2 * kSlot;
   };
-  auto tile = [&](int t, auto k_next, auto v_this, auto load_a, auto load_b) {
-    const int valid = long_tile_valid(tc, tile_at(t)) - 32 * kh;
-    load_a();
-    if (__builtin_expect(valid < 32, 0)) mask_keys(s0, half, valid);
-    {
-      scores(qf[1], s1);
-      const float r0 = exponentials(s0, b0.m, p0);
-      read_k(decltype(k_next)::value);
-      values(p1, b1);
-      add_row_sum(s0, b0, p0, r0);
-    }
-    load_b();
-    if (__builtin_expect(valid < 32, 0)) mask_keys(s1, half, valid);
-    {
-      read_v(decltype(v_this)::value);
-      scores(qf[0], s0);
-      const float r1 = exponentials(s1, b1.m, p1);
-      values(p0, b0);
-      add_row_sum(s1, b1, p1, r1);
-    }
-  };
+  auto tile_keys = [&](int t) { return long_tile_valid(tc, tile_at(t)) - 32 * kh; };  // valid, of the wave's 32
   // Running addresses of the loads of a step at index t: K of index t + 3 and V of t + 2, while
   // those tiles and that of t + 4 follow one another in one part (memory or frame) and are full
   // (t + 4 < run_end).
@@ -805,108 +782,99 @@ __device__ __forceinline__ void process_long_segment(const AttnArgs& a, int q, i
     const int full = mem ? tc.nt_mem - (tc.mem_tail < BK) : tc.t_last + 1 - (tc.tok_tail < BK);
     run_end = uniform(t + 2 + min(full - at, (t + 2 < n_up ? n_up : n) - (t + 2)));
   };
-  // A step computes indices t, t + 1, in ring half y (byte offset 0 or 2 kSlot; z: the other): K
-  // and V tiles t, t + 1 lie in its two slots.  The K fragments are read one tile early, so the
-  // loads of the next pair that go out in a step are K t + 3, t + 4 and V t + 2, t + 3, into
-  // the slots freed at the last barrier.  Full tiles of one part go by running addresses,
-  // others by long_src.
-  uint32_t y = 0;
-  auto loads_a = [&](int t, bool run) {
-    const uint32_t z = 2 * kSlot - y;
-    if (run) {
-      load_rows(v2, off, ring + kVRing + z);
-      load_rows(k3, off, ring + z + kSlot);
-    } else {
-      if (t + 2 < n) {
-        const LongSrc x = long_src(tc, tile_at(t + 2));
-        load_rows(x.v, x, ring + kVRing + z);
-      }
-      if (t + 3 < n) {
-        const LongSrc x = long_src(tc, tile_at(t + 3));
-        load_rows(x.k, x, ring + z + kSlot);
-      }
-    }
-  };
-  auto loads_b = [&](int t, bool run) {
-    const uint32_t z = 2 * kSlot - y;
-    if (run) {
-      load_rows(v2 + step_bytes, off, ring + kVRing + z + kSlot);
-      load_rows(k3 + step_bytes, off, ring + y);
-    } else {
-      if (t + 3 < n) {
-        const LongSrc x = long_src(tc, tile_at(t + 3));
-        load_rows(x.v, x, ring + kVRing + z + kSlot);
-      }
-      if (t + 4 < n) {
-        const LongSrc x = long_src(tc, tile_at(t + 4));
-        load_rows(x.k, x, ring + y);
-      }
-    }
-    k3 += 2 * step_bytes;
-    v2 += 2 * step_bytes;
-  };
-  auto end_step = [&]() {
-    y = 2 * kSlot - y;
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-  };
-  {
-    const LongSrc x0 = long_src(tc, ts);
-    load_rows(x0.k, x0, ring);
-    load_rows(x0.v, x0, ring + kVRing);
-    if (n > 1) {
-      const LongSrc x1 = long_src(tc, tile_at(1));
-      load_rows(x1.k, x1, ring + kSlot);
-      load_rows(x1.v, x1, ring + kVRing + kSlot);
-    }
-    if (n > 2) {
-      const LongSrc x2 = long_src(tc, tile_at(2));
-      load_rows(x2.k, x2, ring + 2 * kSlot);
-    }
-  }
-  // (the query fragments pass through: the compiler's own wait for them belongs here, not in
-  // the loop, where it would be a wait for the tiles in flight)
-  asm volatile("s_waitcnt vmcnt(0)"
-               : "+v"(qf[0][0]), "+v"(qf[0][1]), "+v"(qf[0][2]), "+v"(qf[0][3]), "+v"(qf[1][0]), "+v"(qf[1][1]),
-                 "+v"(qf[1][2]), "+v"(qf[1][3])::"memory");
-  __syncthreads();
-  if (computes) {
-    // The first tile's maxima are the references; its second block's scores are formed again
-    // in the pipeline, and the pipeline's first value product multiplies zeros.
-    const int valid = long_tile_valid(tc, ts) - 32 * kh;
-    read_k(0);
-    scores(qf[1], s1);
-    scores(qf[0], s0);
-    if (valid < 32) mask_keys(s1, half, valid);
-    b1.m = tile_ref(s1);
-    f32x16 sm = s0;
-    if (valid < 32) mask_keys(sm, half, valid);
-    b0.m = tile_ref(sm);
+  // What this wave does at each point of the ring's schedule (long_ring).  A step's loads of
+  // full tiles of one part go by running addresses, others by long_src.
+  bool run = false;
+  auto ops = ring_ops(
+      [&](RingLoadPair x) __attribute__((always_inline)) {
+        const LongSrc src = long_src(tc, tile_at(x.i));
+        load_rows(src.k, src, ring + x.slot * kSlot);
+        load_rows(src.v, src, ring + kVRing + x.slot * kSlot);
+      },
+      [&](RingLoadK x) __attribute__((always_inline)) {
+        const LongSrc src = long_src(tc, tile_at(x.i));
+        load_rows(src.k, src, ring + x.slot * kSlot);
+      },
+      // (the query fragments pass through the first wait: the compiler's own wait for them
+      // belongs there, not in the loop, where it would be a wait for the tiles in flight)
+      [&](RingFirstArrived) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)"
+                     : "+v"(qf[0][0]), "+v"(qf[0][1]), "+v"(qf[0][2]), "+v"(qf[0][3]), "+v"(qf[1][0]),
+                       "+v"(qf[1][1]), "+v"(qf[1][2]), "+v"(qf[1][3])::"memory");
+        __syncthreads();
+      },
+      [&](RingArrived) __attribute__((always_inline)) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+      },
+      [&](RingBarrier) __attribute__((always_inline)) { __syncthreads(); },
+      [&](RingReadFirstK) __attribute__((always_inline)) { read_k(0); },
+      // The first tile's maxima are the references; its second block's scores are formed again
+      // in the pipeline, and the pipeline's first value product multiplies zeros.
+      [&](RingFirstScores) __attribute__((always_inline)) {
+        const int valid = tile_keys(0);
+        scores(qf[1], s1);
+        scores(qf[0], s0);
+        if (valid < 32) mask_keys(s1, half, valid);
+        b1.m = tile_ref(s1);
+        f32x16 sm = s0;
+        if (valid < 32) mask_keys(sm, half, valid);
+        b0.m = tile_ref(sm);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      p1[i] = bf16x8{};
-      vf[i][0] = vf[i][1] = bf16x8{};
-    }
-  }
-  if (computes) {
-    for (int t = 0; t < n; t = uniform(t + 2)) {
-      if (t + 2 >= run_end && t + 2 < n) set_run(t);
-      const bool run = t + 4 < run_end;
-      tile(t, Slot<1>{}, Slot<0>{}, [&] { loads_a(t, run); }, [&] { loads_b(t, run); });
-      flip(ko);
-      if (t + 1 < n) tile(t + 1, Slot<0>{}, Slot<1>{}, [] {}, [] {});
-      flip(vo[0]);
-      flip(vo[1]);
-      end_step();
-    }
-    values(p1, b1);
-  } else {  // a wave without queries only loads
-    for (int t = 0; t < n; t = uniform(t + 2)) {
-      loads_a(t, false);
-      loads_b(t, false);
-      end_step();
-    }
-  }
+        for (int i = 0; i < 2; ++i) {
+          p1[i] = bf16x8{};
+          vf[i][0] = vf[i][1] = bf16x8{};
+        }
+      },
+      [&](RingStep x) __attribute__((always_inline)) {
+        if (x.t + 2 >= run_end && x.t + 2 < n) set_run(x.t);
+        run = x.t + 4 < run_end;
+      },
+      [&](RingLoads x) __attribute__((always_inline)) {
+        if (run) {
+          const uint32_t at = x.second ? step_bytes : 0;
+          load_rows(v2 + at, off, ring + kVRing + x.v_slot * kSlot);
+          load_rows(k3 + at, off, ring + x.k_slot * kSlot);
+        } else {
+          if (x.v < n) {
+            const LongSrc src = long_src(tc, tile_at(x.v));
+            load_rows(src.v, src, ring + kVRing + x.v_slot * kSlot);
+          }
+          if (x.k < n) {
+            const LongSrc src = long_src(tc, tile_at(x.k));
+            load_rows(src.k, src, ring + x.k_slot * kSlot);
+          }
+        }
+        if (x.second) {
+          k3 += 2 * step_bytes;
+          v2 += 2 * step_bytes;
+        }
+      },
+      [&](RingTileA x) __attribute__((always_inline)) {
+        const int valid = tile_keys(x.t);
+        if (__builtin_expect(valid < 32, 0)) mask_keys(s0, half, valid);
+        scores(qf[1], s1);
+        const float r0 = exponentials(s0, b0.m, p0);
+        read_k(x.slot);
+        values(p1, b1);
+        add_row_sum(s0, b0, p0, r0);
+      },
+      [&](RingTileB x) __attribute__((always_inline)) {
+        const int valid = tile_keys(x.t);
+        if (__builtin_expect(valid < 32, 0)) mask_keys(s1, half, valid);
+        read_v(x.slot);
+        scores(qf[0], s0);
+        const float r1 = exponentials(s1, b1.m, p1);
+        values(p0, b0);
+        add_row_sum(s1, b1, p1, r1);
+      },
+      [&](RingFlipK) __attribute__((always_inline)) { flip(ko); },
+      [&](RingFlipV) __attribute__((always_inline)) {
+        flip(vo[0]);
+        flip(vo[1]);
+      });
+  long_ring(n, computes, ops);
+  if (computes) values(p1, b1);
 
   // Each wave keeps one of its query blocks (block kh: rows 32 wave .. + 31 of the unit), takes
   // the other key half's sums of it from the wave beside it, and hands over the other block.

@@ -14,8 +14,18 @@
 #else
 #define RV_HD
 #endif
+#define RV_INLINE inline __attribute__((always_inline))
 
 namespace rv {
+
+// A value that is the same on all lanes of a wave, in a scalar register on the device.
+RV_HD RV_INLINE int wave_uniform(int x) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(x);
+#else
+  return x;
+#endif
+}
 
 constexpr int kHeadDim = 64;     // head dimension supported by every kernel
 constexpr int kAttnBQ = 128;     // queries per attention workgroup (4 waves x 32)
@@ -223,6 +233,86 @@ inline int64_t plan_partial_slots(const AttnPlan& p) { return 2 * (int64_t)p.tot
 // Upper bound on plan_partial_slots of every plan on this device unless RV_ATTN_SPLIT forces
 // a split (a chunk count set by the workgroup slots, whatever the sizes).
 int64_t default_partial_slots(int n_cus, int n_queues);
+
+// ---- the long-chunk kernel's LDS ring ------------------------------------------------
+
+// The schedule of one segment of n tiles (indices 0 .. n - 1) in the long-chunk kernel, as the
+// sequence of operations each wave passes to `ops`.  The kernel executes them; the host checks
+// record them.
+//
+// The ring has four K and four V slots.  A step takes indices t and t + 1, whose K and V tiles
+// lie in the two slots of one ring half.  All four waves write every slot (each its rows of the
+// tile) and read it, so a slot may be refilled only after a barrier that follows its last read:
+// V t, V t + 1 and K t + 1 are read in step t and refilled in the next; K of the next pair is
+// read a tile early (a tile's first half reads the K fragments of the tile after it), so K t + 4
+// goes to the slot of K t within step t.  For the first step, whose K 0 no step before it has
+// read, that takes a barrier of its own after the read.
+//
+// Waves without queries (`computes` false) only load, and pass the same barriers.
+struct RingLoadPair { int i, slot; };        // request K and V of index i into the slot
+struct RingLoadK { int i, slot; };           // request K of index i
+struct RingFirstArrived {};                  // wait for the requests so far, then a barrier
+struct RingArrived {};                       // the same, at a step's end
+struct RingBarrier {};
+struct RingReadFirstK {};                    // read K slot 0
+struct RingFirstScores {};                   // (no ring access)
+struct RingStep { int t; };                  // (no ring access) the loads of step t follow
+struct RingLoads {                           // request V of index v and K of index k, if below n
+  int v, v_slot, k, k_slot;
+  bool second;                               // the second such pair of the step
+};
+struct RingTileA { int t, slot; };           // first half of tile t: reads K slot `slot` of the K half
+struct RingTileB { int t, slot; };           // second half: reads V slot `slot` of the V half
+struct RingFlipK {};                         // reads of K go to the other ring half from here
+struct RingFlipV {};
+
+// One callable of the overloads F.
+template <class... F>
+struct ring_ops_t : F... {
+  using F::operator()...;
+};
+template <class... F>
+RV_HD RV_INLINE ring_ops_t<F...> ring_ops(F... f) {
+  return {f...};
+}
+
+template <class Ops>
+RV_HD RV_INLINE void long_ring(int n, bool computes, Ops& ops) {
+  ops(RingLoadPair{0, 0});
+  if (n > 1) ops(RingLoadPair{1, 1});
+  if (n > 2) ops(RingLoadK{2, 2});
+  ops(RingFirstArrived{});
+  if (computes) ops(RingReadFirstK{});
+  ops(RingBarrier{});
+  int at = 0;  // first slot of the ring half of indices t, t + 1
+  if (computes) {
+    ops(RingFirstScores{});
+    for (int t = 0; t < n; t = wave_uniform(t + 2)) {
+      const int other = 2 - at;
+      ops(RingStep{t});
+      ops(RingLoads{t + 2, other, t + 3, other + 1, false});
+      ops(RingTileA{t, 1});
+      ops(RingLoads{t + 3, other + 1, t + 4, at, true});
+      ops(RingTileB{t, 0});
+      ops(RingFlipK{});
+      if (t + 1 < n) {
+        ops(RingTileA{t + 1, 0});
+        ops(RingTileB{t + 1, 1});
+      }
+      ops(RingFlipV{});
+      at = other;
+      ops(RingArrived{});
+    }
+  } else {
+    for (int t = 0; t < n; t = wave_uniform(t + 2)) {
+      const int other = 2 - at;
+      ops(RingLoads{t + 2, other, t + 3, other + 1, false});
+      ops(RingLoads{t + 3, other + 1, t + 4, at, true});
+      at = other;
+      ops(RingArrived{});
+    }
+  }
+}
 
 // ---- query subset and admission launch shape -------------------------------------------
 

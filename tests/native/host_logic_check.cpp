@@ -7,6 +7,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
+#include <vector>
 
 #include "../../paper_2609_23286_amd/csrc/rv_plan.h"
 
@@ -125,8 +126,88 @@ static void check_tile_swizzle() {
     }
 }
 
+// One wave's accesses to the long-chunk kernel's ring (slots 0..3: K, 4..7: V) between two
+// barriers, and the requests that its next wait covers.
+struct RingInterval {
+  struct Access {
+    int slot, index;
+  };
+  std::vector<Access> requested, read;  // (index -1: a read whose values are not used)
+  bool waits = false;                   // a wait for all requests ends the interval
+};
+
+static std::vector<RingInterval> record_ring(int n, bool computes) {
+  std::vector<RingInterval> iv(1);
+  int k_half = 0, v_half = 0;
+  auto request = [&](int slot, int i) { iv.back().requested.push_back({slot, i}); };
+  auto read = [&](int slot, int i) { iv.back().read.push_back({slot, i < n ? i : -1}); };
+  auto barrier = [&](bool waits) {
+    iv.back().waits = waits;
+    iv.emplace_back();
+  };
+  auto ops = rv::ring_ops(
+      [&](rv::RingLoadPair x) {
+        request(x.slot, x.i);
+        request(4 + x.slot, x.i);
+      },
+      [&](rv::RingLoadK x) { request(x.slot, x.i); }, [&](rv::RingFirstArrived) { barrier(true); },
+      [&](rv::RingArrived) { barrier(true); }, [&](rv::RingBarrier) { barrier(false); },
+      [&](rv::RingReadFirstK) { read(0, 0); }, [&](rv::RingFirstScores) {}, [&](rv::RingStep) {},
+      [&](rv::RingLoads x) {
+        if (x.v < n) request(4 + x.v_slot, x.v);
+        if (x.k < n) request(x.k_slot, x.k);
+      },
+      [&](rv::RingTileA x) { read(k_half + x.slot, x.t + 1); },  // (K is read a tile early)
+      [&](rv::RingTileB x) { read(4 + v_half + x.slot, x.t); }, [&](rv::RingFlipK) { k_half ^= 2; },
+      [&](rv::RingFlipV) { v_half ^= 2; });
+  rv::long_ring(n, computes, ops);
+  return iv;
+}
+
+// The long-chunk kernel's ring, over every segment length that its steps can end in: waves with
+// and without queries pass the same barriers; no slot is read and refilled between the same two;
+// and every read finds the tile it is for, requested by all waves and waited for before.
+static void check_long_ring() {
+  for (int n = 1; n <= 24; ++n) {
+    const std::vector<RingInterval> wave[2] = {record_ring(n, true), record_ring(n, false)};
+    CHECK(wave[0].size() == wave[1].size(), "ring, %d tiles: %zu and %zu barriers", n, wave[0].size(), wave[1].size());
+    if (wave[0].size() != wave[1].size()) continue;
+    int holds[8], pending[8], k_read = 0, v_read = 0;
+    for (int s = 0; s < 8; ++s) holds[s] = pending[s] = -1;
+    for (size_t i = 0; i < wave[0].size(); ++i) {
+      const RingInterval &c = wave[0][i], &idle = wave[1][i];
+      CHECK(idle.read.empty() && c.waits == idle.waits && c.requested.size() == idle.requested.size(),
+            "ring, %d tiles, interval %zu: the waves differ", n, i);
+      for (size_t r = 0; r < c.requested.size() && r < idle.requested.size(); ++r)
+        CHECK(c.requested[r].slot == idle.requested[r].slot && c.requested[r].index == idle.requested[r].index,
+              "ring, %d tiles, interval %zu: the waves request different tiles", n, i);
+      for (const auto& a : c.read) {
+        for (const auto& b : c.requested)
+          CHECK(a.slot != b.slot || a.index < 0, "ring, %d tiles, interval %zu: slot %d is read and refilled (tile %d)",
+                n, i, a.slot, b.index);
+        CHECK(a.index < 0 || holds[a.slot] == a.index, "ring, %d tiles, interval %zu: slot %d holds %d, read as %d", n,
+              i, a.slot, holds[a.slot], a.index);
+        if (a.index >= 0) (a.slot < 4 ? k_read : v_read)++;
+      }
+      for (const auto& b : c.requested) {
+        pending[b.slot] = b.index;
+        holds[b.slot] = -1;
+      }
+      if (c.waits)
+        for (int s = 0; s < 8; ++s)
+          if (pending[s] >= 0) {
+            holds[s] = pending[s];
+            pending[s] = -1;
+          }
+    }
+    CHECK(k_read == n && v_read == n, "ring: %d K and %d V tiles read of %d", k_read, v_read, n);
+    for (int s = 0; s < 8; ++s) CHECK(pending[s] < 0, "ring, %d tiles: a request is never waited for", n);
+  }
+}
+
 int main() {
   check_tile_swizzle();
+  check_long_ring();
   static const int shapes[][4] = {  // n_tokens, n_fkeys, mem_len, n_heads
       {1041, 1041, 0, 16},   {1041, 1041, 1000, 16}, {1041, 1041, 5000, 16}, {1041, 1041, 9990, 16},
       {1041, 1041, 52000, 16}, {1041, 0, 11031, 16}, {1374, 1374, 26000, 16}, {16384, 16384, 3000, 2},
