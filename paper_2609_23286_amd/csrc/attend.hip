@@ -509,7 +509,11 @@ __device__ void process_segment(const AttnArgs& a, int q, int c, int unit, int u
 // 107-109 -> 104-106 us, 52,000 rows 249-259 -> 243-246; 1374 tokens: 20,000 rows 138 -> 131,
 // 52,000 rows 338 -> 309), the same at 40 to 60, and up to 2.5 us more below: the longer
 // prologue, the exchange at the end and odd tiles (1041 tokens, empty memory: 15.3 -> 17.5).
-constexpr float kRefFloor = -1.7e29f;   // lowest softmax reference: above kNegBig * kScaleLog2
+// Added to the scores of keys past a tile's end.  Scaled, it lies below kNegBig, the lowest
+// softmax reference here as in attn_fwd_kernel, so that a wave whose 32 keys are all masked
+// gets p = 0 for each.
+constexpr float kLongMask = -1.0e31f;
+static_assert(kLongMask * kScaleLog2 < kNegBig, "masked keys lie below every reference");
 
 __device__ __forceinline__ const char* uniform_ptr(const char* p) {
   const uint64_t x = reinterpret_cast<uint64_t>(p);
@@ -582,22 +586,21 @@ struct QueryBlock {
   f32x16 o1;    // d = 32..63
 };
 
-// Scores of keys >= valid (of the wave's 32) become -1e30: sat(key + 1 - valid) is 1 exactly
+// Scores of keys >= valid (of the wave's 32) fall by 1e31: sat(key + 1 - valid) is 1 exactly
 // for them, 0 otherwise (arithmetic masking keeps 16 lane masks out of scalar registers).
 // Accumulator entry r of a lane is key 8*(r/4) + 4*half + r%4.
 __device__ __forceinline__ void mask_keys(f32x16& s, int half, int valid) {
   const float fv = (float)(valid - 4 * half - 1);
 #pragma unroll
-  for (int r = 0; r < 16; ++r) s[r] = fmaf(__saturatef((float)(8 * (r >> 2) + (r & 3)) - fv), kNegBig, s[r]);
+  for (int r = 0; r < 16; ++r) s[r] = fmaf(__saturatef((float)(8 * (r >> 2) + (r & 3)) - fv), kLongMask, s[r]);
 }
 
-// Maximum of the 32 keys' scaled scores of each query, at least kRefFloor (a wave whose 32
-// keys are all masked then gets p = 0 for each, not 2^(rounding error of -1e30)).
+// Maximum of the 32 keys' scaled scores of each query, at least kNegBig.
 __device__ __forceinline__ float tile_ref(const f32x16& s) {
   float mx = s[0];
 #pragma unroll
   for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-  return fmaxf(half_max(mx) * kScaleLog2, kRefFloor);
+  return fmaxf(half_max(mx) * kScaleLog2, kNegBig);
 }
 
 // p = 2^(z log2(e) / 8 - m) of one query block's 32 keys, as the value product's operand;

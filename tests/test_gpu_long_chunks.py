@@ -30,6 +30,9 @@ CASES = [  # (N, H, M, split, minimum chunk, per cent of a first chunk, keys)
     # a few units' worth of spread
     (130, 2, 5700, "0", "100", "100", "rising"), (130, 2, 5700, "0", "100", "100", "falling"),
     (70, 2, 5700, "0", "100", "100", "spread"),
+    # logits of -2^97 everywhere (exact in fp32, as is their product with log2(e): every weight is
+    # the same), with a tail of one valid key, whose tile the second key half has none of
+    (66, 2, 5633, "0", "100", "100", "deep"),
 ]
 
 
@@ -55,6 +58,10 @@ def test_long_chunks_match_oracle(N, H, M, split, min_chunk, first_pct, keys, mo
     if keys in ("rising", "falling"):   # logits of standard deviation 0.05 .. 12
         ramp = np.linspace(0.05, 12.0, M)[:: 1 if keys == "rising" else -1]
         memK = synth.f32_to_bf16_bits((bf16_to_f64(memK) * ramp[None, :, None]).astype(np.float32))
+    if keys == "deep":
+        Q, K, memK = (np.zeros_like(x) for x in (Q, K, memK))
+        Q[..., 0] = 0x5880                                  # 2^50
+        K[..., 0] = memK[..., 0] = 0xD880                   # -2^50
     mem = rv.Memory(H, reserve_tokens=M + 5)
     if M:
         mem.write(torch.from_numpy(memK.view(np.int16)), torch.from_numpy(memV.view(np.int16)))
@@ -70,6 +77,15 @@ def test_long_chunks_match_oracle(N, H, M, split, min_chunk, first_pct, keys, mo
     # one, relative, moves the LSE by as much and every weight by that factor.
     z_err = 64 * 2.0 ** -24 * np.abs(want_lse).max()
     assert np.isfinite(got).all() and np.isfinite(got_lse).all()
+    if keys == "deep":
+        # No error in the logits, and the LSE is an fp32 value of that size.  (The output is the
+        # mean of the value rows: at this size exp(z - LSE) loses the log of the keys' number
+        # even in fp64.)
+        rows = np.concatenate((bf16_to_f64(memV), bf16_to_f64(V).transpose(1, 0, 2)), axis=1)
+        want = np.broadcast_to(rows.mean(axis=1)[None], want.shape)
+        assert np.abs(got - want).max() <= out_error_bound(want, vmax)
+        assert np.abs(got_lse - want_lse).max() <= 2.0 ** -22 * np.abs(want_lse).max()
+        return
     assert np.abs(got - want).max() <= out_error_bound(want, vmax) + 2 * z_err * vmax
     if keys == "flat":
         assert np.abs(got - want).max() <= OUT_ATOL
