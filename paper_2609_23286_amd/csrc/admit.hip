@@ -19,10 +19,10 @@
 // select_kernel (Sec. 3.3 Eq. 6, head-specific retention): one workgroup per
 // (layer, head) takes the `budget` largest S_j, equal values ordered by lower index.
 // The order is that of the 64-bit key (bits of S, ~j): fp32 bit patterns order like
-// the values for S >= 0.  Budgets up to kRankedBudget of frames up to kRankedTokens tokens:
-// a lower bound of the budget-th largest value, from the threads' own maxima, leaves a few
-// candidates, which are ranked by counting.  Others, and frames whose ties leave too many
-// candidates: an MSB-first radix select over the bit patterns finds the threshold value and
+// the values for S >= 0.  Small budgets (takes_ranked): a lower bound of the budget-th largest
+// value, from the threads' own maxima, leaves a few candidates, which are ranked by counting.
+// Others, and frames whose largest values lie on so few threads that too many candidates are
+// left: an MSB-first radix select over the bit patterns finds the threshold value and
 // how many of its ties to take, and block scans emit the indices.  Either way the indices
 // come out ascending and the chosen K/V rows are copied to the memory arena at rows
 // mem_len.. with their provenance.
@@ -462,30 +462,48 @@ __device__ __forceinline__ uint32_t wave_sort(uint32_t x, int lane) {
   return exchange<1, 1>(x, lane);
 }
 
-// Top-`budget` (budget <= kRankedBudget, budget < N <= kRankedTokens), ascending, into s_idx;
-// v[m] is the value of token tid + NT m.  The budget-th largest of the 256 threads' maxima is
-// no larger than the budget-th largest value, so the tokens at or above it hold the
-// selection: budget threads' tokens at most, without ties.  They are gathered (in any order:
-// the keys are distinct), each one's rank is the number of larger keys, and the place of a
-// winner is the number of winners with a lower index.  False, on every thread, if more than
-// `cap` tokens are at or above the bound (many equal values).
+// Whether the selection ranks its candidates (select_ranked) or takes the radix way.  The lines:
+// kLaneSlots values in registers, and a budget up to which the counts take less than the radix
+// way (selection alone, 256 heads, budgets 64 / 96 / 128: 257 tokens 8.7 / 10.6 / 13.5 us ranked,
+// 8.6 / 9.4 / 10.4 radix; 1041 tokens 9.1 / 11.3 / 13.8 and 10.6 / 11.0 / 12.0; 2048 tokens 9.1 /
+// 11.5 / 13.6 and 11.8 / 12.8 / 13.9); of few tokens, no more than half, which is the room for
+// candidates.
+constexpr int kLaneSlots = 8;
+constexpr int kRankedTokens = NT * kLaneSlots;
+constexpr int kRankedBudget = 128;
+__device__ __forceinline__ bool takes_ranked(int N, int budget) {
+  return N <= kRankedTokens && 2 * budget <= N && budget <= 40 + N / 24;
+}
+static_assert(40 + kRankedTokens / 24 <= kRankedBudget && kRankedBudget <= NT, "one thread a winner");
+
+// Candidates that are ranked, at most: one a thread.  (More would take a second round of counts:
+// 256 candidates at budget 10 take 11 us, 320 take 16, as long as the radix way after the attempt.)
+constexpr int kMaxCandidates = NT;
+// Equal values from which they are cut to those needed.  (It takes about 2.5 us, as long as
+// counting over 100 more candidates.  All tokens equal, 1041 tokens: 8.8 us at budget 1, 9.3 at
+// 10; without the cut, through the radix way, 15.5 and 15.2.)
+constexpr int kManyEqual = 64;
+
+// Top-`budget` (takes_ranked), ascending, into s_idx; v[m] is the value of token tid + NT m.  The
+// budget-th largest of the 256 threads' maxima is no larger than the budget-th largest value, so
+// the tokens at or above it hold the selection: budget threads' tokens at most, and those equal
+// to the bound.  Where the latter are many, the tokens above the bound are counted exactly and
+// only the first equal ones that the budget still needs are candidates.  The candidates are
+// gathered into s_cand (in any order: the keys are distinct), each one's rank is the number of
+// larger keys, and the place of a winner is the number of winners with a lower index.  False, on
+// every thread, if there are more than `cap` candidates.
 // What bounds it is the chain of dependent steps, one wave per SIMD.  (Before: `budget`
 // rounds of wave-wide maxima in each wave and again over their winners, or, above 32, the
 // radix select.  The selection launch for 24 layers of 1041 tokens: 9.7 -> 5.9 us at budget
 // 10, 15.0 -> 10.4 at 52; one layer 8.4 -> 5.6; an empty launch takes 2.4.  Reading eight
-// keys a step in the counts: 6.6 and 12.1.)  The lines: kLaneSlots values in registers, and a
-// budget at which the counts still take less than the radix select (admission of 24 layers at
-// budget 128: 43.0 us against 44.9 by radix; the gain shrinks from 5 us at 52).
-constexpr int kRankedBudget = 128;
-constexpr int kLaneSlots = 8;
-constexpr int kRankedTokens = NT * kLaneSlots;
-
-__device__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, int32_t* s_idx, uint64_t* s_cand,
-                              int cap) {
+// keys a step in the counts: 6.6 and 12.1.)
+__device__ __forceinline__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, int32_t* s_idx,
+                                              uint64_t* s_cand, int cap) {
+  __shared__ uint64_t s_equal[kLaneSlots * NW];  // tokens equal to the bound, a bit each, in order
   __shared__ uint32_t s_sorted[NT];
   __shared__ int32_t s_win[kRankedBudget];
   __shared__ uint32_t s_bound;
-  __shared__ int s_count;
+  __shared__ int s_count[3];  // tokens at or above the bound | equal ones << 16; candidates; tokens above the bound
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t best = 0u;  // (threads without tokens rank last: budget < N)
 #pragma unroll
@@ -493,7 +511,7 @@ __device__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, i
     if (tid + NT * m < N) best = max(best, __float_as_uint(v[m]));
   const uint32_t x = wave_sort(best, lane);
   s_sorted[tid] = x;
-  if (tid == 0) s_count = 0;
+  if (tid < 3) s_count[tid] = 0;
   __syncthreads();
   // Rank of x among all 256, equal values in the order of waves then lanes.
   int rank = lane;
@@ -513,20 +531,58 @@ __device__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, i
   if (rank == budget - 1) s_bound = x;
   __syncthreads();
   const uint32_t bound = s_bound;
-  int n = 0;
+  // (bit m: the thread's m-th token)
+  uint32_t above = 0u, equal = 0u;
 #pragma unroll
-  for (int m = 0; m < kLaneSlots; ++m) n += tid + NT * m < N && __float_as_uint(v[m]) >= bound;
-  if (n > 0) {
-    int at = atomicAdd(&s_count, n);
+  for (int m = 0; m < kLaneSlots; ++m) {
+    const uint32_t b = __float_as_uint(v[m]);
+    above |= (uint32_t)(tid + NT * m < N && b > bound) << m;
+    equal |= (uint32_t)(tid + NT * m < N && b == bound) << m;
+  }
+  auto gather = [&](uint32_t in, int at) {
 #pragma unroll
     for (int m = 0; m < kLaneSlots; ++m)
-      if (tid + NT * m < N && __float_as_uint(v[m]) >= bound) {
+      if (in >> m & 1u) {
         if (at < cap) s_cand[at] = rank_key(v[m], tid + NT * m);
         ++at;
       }
-  }
+  };
+  if (above | equal)
+    gather(above | equal, atomicAdd(&s_count[0], __popc(above | equal) + (__popc(equal) << 16)) & 0xFFFF);
   __syncthreads();
-  const int nc = s_count;
+  int nc = s_count[0] & 0xFFFF;
+  const int n_equal = s_count[0] >> 16;
+  if (nc > 2 * budget && n_equal > kManyEqual) {  // uniform
+    int n_above = 0;
+#pragma unroll
+    for (int m = 0; m < kLaneSlots; ++m) {
+      const uint64_t eq = __ballot(equal >> m & 1u);
+      n_above += __popcll(__ballot(above >> m & 1u));
+      if (lane == 0) s_equal[m * NW + wave] = eq;  // tokens NT m + 64 wave ..
+    }
+    if (lane == 0 && n_above) atomicAdd(&s_count[2], n_above);
+    __syncthreads();
+    const int need = budget - s_count[2];
+    // Equal tokens before word l, on lane l.
+    const int own = lane < kLaneSlots * NW ? __popcll(s_equal[lane]) : 0;
+    int before = own;
+#pragma unroll
+    for (int off = 1; off < kLaneSlots * NW; off <<= 1) {
+      const int u = __shfl_up(before, off);
+      if (lane >= off) before += u;
+    }
+    before -= own;
+    uint32_t in = above;
+#pragma unroll
+    for (int m = 0; m < kLaneSlots; ++m) {
+      const int first = __shfl(before, m * NW + wave);
+      const uint64_t word = s_equal[m * NW + wave];
+      if ((equal >> m & 1u) && first + __popcll(word & ((1ull << lane) - 1)) < need) in |= 1u << m;
+    }
+    if (in) gather(in, atomicAdd(&s_count[1], __popc(in)));
+    __syncthreads();
+    nc = s_count[1];
+  }
   if (nc > cap) {  // uniform
     __syncthreads();  // (s_cand is the caller's again)
     return false;
@@ -591,24 +647,33 @@ __global__ __launch_bounds__(NT) void select_kernel(AdmitArgs a) {
       for (int m = 0; m < M; ++m)
         if (j0 + NT * m < N) L.sal_out[(int64_t)h_own * N + j0 + NT * m] = acc[m];
   };
-  if (k <= kRankedBudget && k < N && N <= kRankedTokens) {  // uniform
-    float v[kLaneSlots];
+  bool ranked = false;
+  float v[kLaneSlots];
+  const bool few = takes_ranked(N, k);  // uniform
+  if (few) {
     values(tid, v);
-    // (the candidates lie where the values would: N / 2 keys)
-    if (!select_ranked(v, N, k, s_idx, reinterpret_cast<uint64_t*>(s_sal), N / 2)) {
+    // (the candidates lie where the values would)
+    ranked = select_ranked(v, N, k, s_idx, reinterpret_cast<uint64_t*>(s_sal), min(kMaxCandidates, N / 2));
+  }
+  if (!ranked) {  // uniform
+    if (few) {
 #pragma unroll
       for (int m = 0; m < kLaneSlots; ++m)
         if (tid + NT * m < N) s_sal[tid + NT * m] = v[m];
-      __syncthreads();
-      select_topk(s_sal, N, k, s_idx);
-    }
-  } else {
-    for (int j0 = tid; j0 < N; j0 += NT * kLaneSlots) {
-      float v[kLaneSlots];
-      values(j0, v);
+    } else if (a.shared_select || a.sal_tiles > 0) {
+      for (int j0 = tid; j0 < N; j0 += NT * kLaneSlots) {
+        values(j0, v);
 #pragma unroll
-      for (int m = 0; m < kLaneSlots; ++m)
-        if (j0 + NT * m < N) s_sal[j0 + NT * m] = v[m];
+        for (int m = 0; m < kLaneSlots; ++m)
+          if (j0 + NT * m < N) s_sal[j0 + NT * m] = v[m];
+      }
+    } else if ((N & 3) == 0) {  // (+ 0: as the sums, -0 ranks as 0)
+      for (int j = tid; j < N / 4; j += NT) {
+        const float4 x = reinterpret_cast<const float4*>(rows)[j];
+        reinterpret_cast<float4*>(s_sal)[j] = make_float4(x.x + 0.f, x.y + 0.f, x.z + 0.f, x.w + 0.f);
+      }
+    } else {
+      for (int j = tid; j < N; j += NT) s_sal[j] = rows[j] + 0.f;
     }
     __syncthreads();
     select_topk(s_sal, N, k, s_idx);

@@ -19,6 +19,17 @@ CASES = [  # (N, budget, values)
     # ties: few levels (more candidates than fit: the radix way), half the tokens equal at
     # the bound, all equal, all zero, zeros below a few values
     (1041, 10, "levels"), (1041, 52, "half equal"), (1041, 10, "equal"), (200, 128, "zero"), (1041, 52, "few"),
+    # the largest budget that is ranked for a frame, and one more (40 + N / 24; half the tokens)
+    (1041, 83, "spread"), (1041, 84, "spread"), (2048, 125, "spread"), (2048, 126, "spread"), (80, 40, "spread"),
+    (80, 41, "spread"), (2, 1, "zero"),
+    # equal values cut to those the budget needs: in every word of 64 tokens, in the last one only,
+    # more values above the bound than the budget (threads hold several), and none needed
+    (2048, 125, "half equal"), (2047, 1, "equal"), (2048, 70, "zero"), (2040, 60, "last equal"),
+    (2048, 40, "clump equal"),
+    # more candidates than fit, none of them equal
+    (2048, 52, "clump"), (1041, 83, "clump"),
+    # -0 is 0, ranked and by radix
+    (1041, 10, "signed zeros"), (2050, 10, "signed zeros"), (2052, 10, "signed zeros"),
 ]
 
 
@@ -41,6 +52,17 @@ def saliency(N, values, rng):
         s = np.full(N, 0.25)
     elif values == "zero":
         s = np.zeros(N)
+    elif values == "last equal":    # 58 spread ones, and the last 60 tokens equal
+        s = rng.random(N) * 0.5
+        s[rng.choice(N - 60, 58, replace=False)] = 2.0 + rng.random(58)
+        s[N - 60 + rng.choice(60, 60, replace=False)] = 1.0
+    elif values in ("clump", "clump equal"):    # all of the largest values on fewer threads than the budget
+        s = rng.random(N) * 0.5 + (np.arange(N) % 256 < (51 if values == "clump" else 30))
+        if values == "clump equal":             # ... and the bound a value that 200 others hold
+            s[rng.choice(np.flatnonzero(np.arange(N) % 256 >= 40), 200, replace=False)] = 0.75
+    elif values == "signed zeros":
+        s = np.where(rng.random(N) < 0.5, 0.0, -0.0)
+        s[rng.choice(N, 4, replace=False)] = 1.0
     elif values == "few":
         s = np.zeros(N)
         s[rng.choice(N, 40, replace=False)] = 1.0
