@@ -1077,11 +1077,16 @@ __global__ __launch_bounds__(kAttnThreads) void attn_merge_kernel(AttnArgs a) {
 //   blocks, then across the lane halves -- into tiles[h][qt][j].
 // What bounds it is latency: the merge's round trips (4.8 us alone), then each wave's chain of
 // (key block, query block) steps.  So the key and query rows are requested ahead of the
-// merge's partials and the wave's two or three key blocks go through each query block
-// together: 11.7 -> 10.8 us a launch (1041 tokens, 16 heads, 3,210 rows remembered).
+// merge's partials and the wave's key blocks go through each query block two at a time (1041
+// tokens, 16 heads, 5,000 rows remembered: 11.2 -> 9.3 us a launch; three at a time 10.0, and
+// where a wave has four blocks, three and one took longer than before: 2000 tokens, 8 heads,
+// 10.2 -> 10.8 and, by two, 9.6).  That takes more than 128 registers, so three workgroups fit a
+// CU.  A launch that four to a CU would carry in fewer rounds keeps the form with fewer registers
+// (attn_merge_sal_late_kernel: rows requested when they are needed, one block at a time): 2000
+// tokens, 16 heads, 1,024 workgroups: 17.1 us, and 20.2 with the rows requested early.
 constexpr int kEpiGroups = 4;
 constexpr int kEpiQStride = kHeadDim + 8;   // staged query rows, 144 bytes
-constexpr int kEpiKeyBatch = 3;             // 32-key blocks whose K rows a wave loads together
+constexpr int kEpiEarlyPerCu = 3, kEpiLatePerCu = 4;   // workgroups that fit a CU
 
 // Final LSE (log2 units) of row `row` of a split unit, with merge_rows' arithmetic.
 __device__ float merged_lse2(const AttnArgs& a, int q, int ui, int row, int c_first, int c_last) {
@@ -1106,7 +1111,8 @@ __device__ float merged_lse2(const AttnArgs& a, int q, int ui, int row, int c_fi
   return mmax + __log2f(L);
 }
 
-__global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArgs a, SalEpi e) {
+template <bool kEarly>
+__device__ __forceinline__ void merge_sal_body(const AttnArgs& a, const SalEpi& e) {
   __shared__ float s_lse2[BQ];                        // by row
   __shared__ float s_lsec[BQ];                        // by sampled position (padding: +inf)
   __shared__ int s_list[BQ];
@@ -1123,6 +1129,18 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArg
   const int N = a.n_tokens;
   const int c_first = chunk_holding(a, (int64_t)ui * a.U);
   const int c_last = chunk_holding(a, (int64_t)ui * a.U + a.T - 1);
+
+  // ---- this group's output rows, and the LSE of all the block's rows ----
+  auto merge = [&]() __attribute__((always_inline)) {
+    if (c_first != c_last) merge_rows(a, q, unit, ui, g, c_first, c_last);
+    if (tid < BQ) {
+      const int qi = qt * BQ + tid;
+      float l2 = 0.f;
+      if (qi < N) l2 = c_first == c_last ? a.lse[(int64_t)h * N + qi] * kLog2e : merged_lse2(a, q, ui, tid, c_first, c_last);
+      s_lse2[tid] = l2;
+    }
+  };
+  if (!kEarly) merge();
 
   // ---- the block's sampled queries, in row order (waves 0 and 1 hold rows 0 .. 127) ----
   const int srow = wave * 64 + lane;
@@ -1148,12 +1166,13 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArg
   const int blk0 = g * per_group, blk1 = min(n_blocks, blk0 + per_group);
 
   constexpr int kWaves = kAttnThreads / 64;
-  // ---- everything the saliency reads, requested before the merge's partials: the key rows
-  // of the wave's first blocks and the sampled query rows (clamped, valid addresses) ----
-  bf16x8 kf[kEpiKeyBatch][4];
+  // ---- kEarly: everything the saliency reads, requested before the merge's partials: the key
+  // rows of the wave's first blocks and the sampled query rows (clamped, valid addresses) ----
+  constexpr int kKeyBatch = kEarly ? 2 : 4;  // 32-key blocks whose K rows a wave loads together
+  bf16x8 kf[kKeyBatch][4];
   auto load_k = [&](int kb0) {
 #pragma unroll
-    for (int bb = 0; bb < kEpiKeyBatch; ++bb) {
+    for (int bb = 0; bb < kKeyBatch; ++bb) {
       const int j = min((kb0 + bb * kWaves) * 32 + l32, N - 1);  // past the range: result unused
       const uint16_t* kp = Kh + (int64_t)j * e.kv_row + half * 8;
 #pragma unroll
@@ -1161,45 +1180,44 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArg
     }
   };
   constexpr int kRowLoads = BQ * 8 / kAttnThreads;
+  auto q_row = [&](int x) {  // 16-byte chunk x % 8 of the x / 8-th sampled query
+    const int row = s_list[min(x >> 3, n_s - 1)];
+    return *reinterpret_cast<const uint4*>(a.Q + ((int64_t)(qt * BQ + row) * a.n_heads + h) * D + (x & 7) * 8);
+  };
   uint4 qv[kRowLoads];
-  if (n_s > 0) {
+  if (kEarly && n_s > 0) {
     load_k(blk0 + wave);
 #pragma unroll
-    for (int i = 0; i < kRowLoads; ++i) {
-      const int x = tid + i * kAttnThreads, row = s_list[min(x >> 3, n_s - 1)];
-      qv[i] = *reinterpret_cast<const uint4*>(a.Q + ((int64_t)(qt * BQ + row) * a.n_heads + h) * D + (x & 7) * 8);
-    }
+    for (int i = 0; i < kRowLoads; ++i) qv[i] = q_row(tid + i * kAttnThreads);
   }
 
-  // ---- this group's output rows, and the LSE of all the block's rows ----
-  if (c_first != c_last) merge_rows(a, q, unit, ui, g, c_first, c_last);
-  if (tid < BQ) {
-    const int qi = qt * BQ + tid;
-    float l2 = 0.f;
-    if (qi < N) l2 = c_first == c_last ? a.lse[(int64_t)h * N + qi] * kLog2e : merged_lse2(a, q, ui, tid, c_first, c_last);
-    s_lse2[tid] = l2;
-  }
+  if (kEarly) merge();
   if (n_s == 0) {  // no sampled query in this block: its saliency row is the empty sum
     for (int j = blk0 * 32 + tid; j < min(N, blk1 * 32); j += kAttnThreads) tile_h[j] = 0.f;
     return;
   }
   // sampled query rows and their LSE (padding rows: zero rows, +inf -> weight 0)
+  auto stage = [&](int x, const uint4& v) {
+    *reinterpret_cast<uint4*>(&s_q[(x >> 3) * kEpiQStride + (x & 7) * 8]) = (x >> 3) < n_s ? v : uint4{0u, 0u, 0u, 0u};
+  };
+  if constexpr (kEarly) {
 #pragma unroll
-  for (int i = 0; i < kRowLoads; ++i) {
-    const int x = tid + i * kAttnThreads, s = x >> 3;
-    if (s < ns_pad) *reinterpret_cast<uint4*>(&s_q[s * kEpiQStride + (x & 7) * 8]) = s < n_s ? qv[i] : uint4{0u, 0u, 0u, 0u};
+    for (int i = 0; i < kRowLoads; ++i)
+      if (tid + i * kAttnThreads < ns_pad * 8) stage(tid + i * kAttnThreads, qv[i]);
+  } else {
+    for (int x = tid; x < ns_pad * 8; x += kAttnThreads) stage(x, q_row(x));
   }
   __syncthreads();
   for (int s = tid; s < ns_pad; s += kAttnThreads) s_lsec[s] = s < n_s ? s_lse2[s_list[s]] : __builtin_inff();
   __syncthreads();
 
-  // ---- this group's key blocks, kEpiKeyBatch per wave at a time: each sampled query block's
-  // rows and LSE are read once for all of them, and their MFMA and exponential chains are
-  // independent ----
-  for (int kb0 = blk0 + wave; kb0 < blk1; kb0 += kEpiKeyBatch * kWaves) {
-    if (kb0 != blk0 + wave) load_k(kb0);
-    auto sweep = [&](auto nb_c) {
-      constexpr int NB = decltype(nb_c)::value;
+  // ---- this group's key blocks, kKeyBatch per wave at a time; kEarly: the two go through each
+  // sampled query block together, its rows and LSE read once for both, their MFMA and
+  // exponential chains independent ----
+  for (int kb0 = blk0 + wave; kb0 < blk1; kb0 += kKeyBatch * kWaves) {
+    if (!kEarly || kb0 != blk0 + wave) load_k(kb0);
+    auto sweep = [&](auto first_c, auto nb_c) {  // blocks first .. first + NB - 1 of the batch
+      constexpr int F = decltype(first_c)::value, NB = decltype(nb_c)::value;
       float acc[NB] = {};
       for (int qb = 0; qb < ns_pad; qb += 32) {
         bf16x8 qf[4];
@@ -1214,7 +1232,7 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArg
 #pragma unroll
         for (int ds = 0; ds < 4; ++ds)
 #pragma unroll
-          for (int bb = 0; bb < NB; ++bb) z[bb] = mfma32(qf[ds], kf[bb][ds], z[bb]);
+          for (int bb = 0; bb < NB; ++bb) z[bb] = mfma32(qf[ds], kf[F + bb][ds], z[bb]);
 #pragma unroll
         for (int bb = 0; bb < NB; ++bb) {
           float s0 = 0.f, s1 = 0.f;
@@ -1229,18 +1247,30 @@ __global__ __launch_bounds__(kAttnThreads, 3) void attn_merge_sal_kernel(AttnArg
 #pragma unroll
       for (int bb = 0; bb < NB; ++bb) {
         const float tot = acc[bb] + __shfl_xor(acc[bb], 32);
-        const int j = (kb0 + bb * kWaves) * 32 + l32;
+        const int j = (kb0 + (F + bb) * kWaves) * 32 + l32;
         if (half == 0 && j < N) tile_h[j] = tot;
       }
     };
-    static_assert(kEpiKeyBatch == 3, "a batch holds one to three blocks");
-    if (kb0 + 2 * kWaves < blk1)  // uniform
-      sweep(std::integral_constant<int, 3>{});
-    else if (kb0 + kWaves < blk1)
-      sweep(std::integral_constant<int, 2>{});
-    else
-      sweep(std::integral_constant<int, 1>{});
+    using std::integral_constant;
+    if constexpr (kEarly) {
+      if (kb0 + kWaves < blk1)  // uniform
+        sweep(integral_constant<int, 0>{}, integral_constant<int, 2>{});
+      else
+        sweep(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+    } else {
+      sweep(integral_constant<int, 0>{}, integral_constant<int, 1>{});
+      if (kb0 + kWaves < blk1) sweep(integral_constant<int, 1>{}, integral_constant<int, 1>{});  // uniform
+      if (kb0 + 2 * kWaves < blk1) sweep(integral_constant<int, 2>{}, integral_constant<int, 1>{});
+      if (kb0 + 3 * kWaves < blk1) sweep(integral_constant<int, 3>{}, integral_constant<int, 1>{});
+    }
   }
+}
+
+__global__ __launch_bounds__(kAttnThreads, kEpiEarlyPerCu) void attn_merge_sal_kernel(AttnArgs a, SalEpi e) {
+  merge_sal_body<true>(a, e);
+}
+__global__ __launch_bounds__(kAttnThreads, kEpiLatePerCu) void attn_merge_sal_late_kernel(AttnArgs a, SalEpi e) {
+  merge_sal_body<false>(a, e);
 }
 
 __global__ void xcc_probe_kernel(int* ids) {
@@ -1276,14 +1306,18 @@ hipError_t launch_attention(const AttnArgs& a, int grid, bool merge, bool long_c
   return hipGetLastError();
 }
 
-hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, bool long_chunks,
+hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, bool long_chunks, int n_cus,
                                      hipStream_t s) {
   hipError_t err = launch_forward(a, grid, long_chunks, s);
   if (err != hipSuccess) return err;
   int max_units = 0;
   for (int q = 0; q < a.n_queues; ++q) max_units = max(max_units, a.unit_base[q + 1] - a.unit_base[q]);
-  hipLaunchKernelGGL(attn_merge_sal_kernel, dim3(a.n_queues * max_units * kEpiGroups), dim3(kAttnThreads), 0, s,
-                     a, e);
+  // (rounds of an XCD's workgroups on its CUs)
+  const int n_wg = max_units * kEpiGroups, cus = max(1, n_cus / a.n_queues);
+  const bool late = (n_wg + kEpiLatePerCu * cus - 1) / (kEpiLatePerCu * cus) <
+                    (n_wg + kEpiEarlyPerCu * cus - 1) / (kEpiEarlyPerCu * cus);
+  hipLaunchKernelGGL(late ? attn_merge_sal_late_kernel : attn_merge_sal_kernel, dim3(a.n_queues * n_wg),
+                     dim3(kAttnThreads), 0, s, a, e);
   return hipGetLastError();
 }
 

@@ -579,7 +579,8 @@ rv_status attend_impl(const void* Q, const void* K, const void* V, int n_tokens,
     e.grid_w = qs->grid_w > 0 ? qs->grid_w : 1;
     e.grid_cells = qs->grid_h * qs->grid_w;
     e.stride = qs->stride;
-    RV_HIP(rv::launch_attention_saliency(a, e, p.grid, rv::plan_long_chunks(p, n_tokens), s), "attention launch");
+    RV_HIP(rv::launch_attention_saliency(a, e, p.grid, rv::plan_long_chunks(p, n_tokens), ws->n_cus, s),
+           "attention launch");
     return RV_OK;
   }
   // every unit whole in one chunk (no split) needs no merge launch

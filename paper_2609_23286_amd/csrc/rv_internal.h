@@ -14,7 +14,7 @@ hipError_t launch_attention(const AttnArgs& a, int grid, bool merge, bool long_c
 // The attention launch with the saliency in its epilogue: the forward launch, then one
 // merge workgroup per unit that forms the unit's outputs and LSE (when its key range was
 // split) and then the unit's row of per-block saliency (SalEpi).
-hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, bool long_chunks,
+hipError_t launch_attention_saliency(const AttnArgs& a, const SalEpi& e, int grid, bool long_chunks, int n_cus,
                                      hipStream_t s);
 // Device address, on the current device, of the library's static partial-slot array
 // (kStaticScratchSlots slots of kAttnSlotFloats floats).

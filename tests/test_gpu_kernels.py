@@ -636,6 +636,13 @@ FUSED_CASES = [  # (N, H, M, qs, plan overrides): ragged blocks, empty memory, a
     (1, 1, 0, (1, 1, 0, 1), {}),
     (400, 2, 200, (0, 10, 400, 2), {}),                     # empty subset: every row 0
     (333, 4, 1500, (9, 37, 0, 2), {"RV_ATTN_WG_PER_CU": "1", "RV_ATTN_MIN_CHUNK": "100000"}),
+    # four and three 32-key blocks a wave, few workgroups and (16 heads) a launch that four to a
+    # CU carry in one round; five blocks a wave
+    (2000, 3, 100, (40, 50, 0, 2), {}),
+    (1601, 16, 300, (40, 40, 1, 1), {}),
+    (2016, 16, 0, (42, 48, 0, 3), {}),
+    (1600, 16, 50, (0, 10, 1600, 2), {}),
+    (2500, 12, 64, (50, 50, 0, 4), {}),
 ]
 
 
