@@ -183,17 +183,28 @@ int admit_max_dynamic_lds(int max_lds) { return max_lds - kAdmitStaticLdsMargin;
 
 void plan_saliency(AdmitArgs* a, int n_lh, int n_cus, int max_lds) {
   // About three 4-wave workgroups per CU over the launch, each wave taking blocks two at a
-  // time; or one block a wave, where the launch then still fits four workgroups per CU (124
-  // registers a wave instead of 167).  7 layers of 1041 tokens, saliency and selection: 18.9 us
-  // with one block a wave (1008 workgroups), 23.2 with up to two (784); every patch sampled:
-  // 47.6 and 62.1.  Beyond that the launch would take a second round of workgroups, each
-  // staging the query rows again.
+  // time, or one block a wave.  Three workgroups are resident on a CU (their LDS: q_pass below),
+  // and the workgroups of ceil(n_lh / XCDs) heads share an XCD's CUs; a second round of them
+  // costs more than one block a wave gains.  So one block a wave is taken where its workgroups
+  // fit one round, or where two at a time need a second round as well (up to four workgroups per
+  // CU).  Saliency alone, two -> one: 5 layers of 1041 tokens, 16 heads (one round each) 14.0 ->
+  // 12.0 us, every patch sampled 40.8 -> 32.8; 7 layers (two rounds each) 19.4 -> 15.4 and 61.2 ->
+  // 47.0; 6 layers (one round, two) 14.4 -> 15.2 and 42.0 -> 45.5.
   constexpr int kWaves = kAdmitThreads / 64;
   const int n_blocks = (a->n_tokens + 31) / 32;
-  const int max_groups = (n_blocks + kWaves - 1) / kWaves;
+  const int xcds = a->sal_xcds > 0 ? a->sal_xcds : 1;
+  const int64_t heads = (n_lh + xcds - 1) / xcds, resident = 3 * (n_cus / xcds);
+  auto groups_held = [&](int g) {  // of g groups, those that hold blocks
+    const int per = (n_blocks + g - 1) / g;
+    return per > 0 ? (n_blocks + per - 1) / per : 1;
+  };
+  const int g_one = n_blocks > kWaves ? (n_blocks + kWaves - 1) / kWaves : 1;
+  const int g_max = n_blocks / kWaves > 1 ? n_blocks / kWaves : 1;
   const int g = (3 * n_cus + n_lh - 1) / (n_lh > 0 ? n_lh : 1);
-  const bool one = (int64_t)n_lh * max_groups <= (int64_t)4 * n_cus;
-  a->sal_groups = one || g > max_groups ? max_groups : g < 1 ? 1 : g;
+  const int g_two = g < 1 ? 1 : g > g_max ? g_max : g;
+  const bool one = heads * g_one <= resident ||
+                   (heads * groups_held(g_two) > resident && (int64_t)n_lh * g_one <= (int64_t)4 * n_cus);
+  a->sal_groups = one ? g_one : g_two;
   // Sampled query rows are staged in passes of q_pass rows, sized so that three
   // workgroups fit a CU's LDS; the pass size depends only on n_q and the device, so
   // every launch of the same frame shape sums in the same order.  An empty subset has

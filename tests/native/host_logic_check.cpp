@@ -103,6 +103,25 @@ static void check_saliency(int grid_h, int grid_w, int n_special, int stride, in
   }
 }
 
+// Which saliency launches take one block a wave (more workgroups than three to a CU of its XCD
+// only where two blocks at a time need a second round as well).
+static void check_saliency_line() {
+  static const int rows[][3] = {  // tokens, (layer, head) pairs, groups expected
+      {1041, 16, 9},  {1041, 80, 9},   // one round of one block a wave
+      {1041, 84, 8},  {1041, 96, 8},   // one round by twos, two of one block
+      {1041, 112, 9}, {1041, 108, 9},  // two rounds either way
+      {1041, 128, 6}, {1041, 384, 2},  // past four workgroups a CU
+      {1374, 64, 11}, {1374, 80, 10}, {1374, 84, 11}, {2030, 48, 16}, {2030, 64, 12}, {64, 384, 1}};
+  for (const auto& r : rows) {
+    rv::AdmitArgs a{};
+    a.n_tokens = r[0];
+    a.n_q = 266;
+    a.sal_xcds = 8;
+    rv::plan_saliency(&a, r[1], 256, 163840);
+    CHECK(a.sal_groups == r[2], "%d tokens, %d pairs: %d groups, expected %d", r[0], r[1], a.sal_groups, r[2]);
+  }
+}
+
 // The attention tiles' LDS swizzle: distinct chunks on every 8 aligned rows (the K reads
 // of 8 lanes, one row each, at 128 bytes a cycle) and distinct (row parity, chunk) pairs
 // on every 16 (16 lanes at 256 bytes a cycle); and every aligned group of 4 rows puts a
@@ -208,6 +227,7 @@ static void check_long_ring() {
 int main() {
   check_tile_swizzle();
   check_long_ring();
+  check_saliency_line();
   static const int shapes[][4] = {  // n_tokens, n_fkeys, mem_len, n_heads
       {1041, 1041, 0, 16},   {1041, 1041, 1000, 16}, {1041, 1041, 5000, 16}, {1041, 1041, 9990, 16},
       {1041, 1041, 52000, 16}, {1041, 0, 11031, 16}, {1374, 1374, 26000, 16}, {16384, 16384, 3000, 2},
