@@ -351,6 +351,9 @@ typedef struct rv_attn_plan {
 } rv_attn_plan;
 rv_status rv_attention_plan(int n_tokens, int n_fkeys, int64_t mem_len, int n_heads, int n_cus,
                             int n_queues, rv_attn_plan *out);
+/* 1 if a launch of this plan takes the forward kernel for long chunks (attn_long_kernel), 0 if
+ * it takes attn_fwd_kernel.  Results are the same within rounding. */
+int rv_attention_plan_long(const rv_attn_plan *plan);
 
 /* Grows the current device's scratch workspace (calling rv_init first if needed): the
  * split-KV partial slots of the work plan for frames of n_tokens tokens and n_heads heads

@@ -481,6 +481,10 @@ rv_status rv_attention_plan(int n_tokens, int n_fkeys, int64_t mem_len, int n_he
   return RV_OK;
 }
 
+int rv_attention_plan_long(const rv_attn_plan* plan) {
+  return plan && plan->E > 0 && rv::plan_long_chunks(*plan) ? 1 : 0;
+}
+
 rv_status rv_init(void) {
   std::lock_guard<std::mutex> lk(g_ws_mu);
   Workspace* ws;
@@ -579,12 +583,12 @@ rv_status attend_impl(const void* Q, const void* K, const void* V, int n_tokens,
     e.grid_w = qs->grid_w > 0 ? qs->grid_w : 1;
     e.grid_cells = qs->grid_h * qs->grid_w;
     e.stride = qs->stride;
-    RV_HIP(rv::launch_attention_saliency(a, e, p.grid, rv::plan_long_chunks(p, n_tokens), ws->n_cus, s),
+    RV_HIP(rv::launch_attention_saliency(a, e, p.grid, rv::plan_long_chunks(p), ws->n_cus, s),
            "attention launch");
     return RV_OK;
   }
   // every unit whole in one chunk (no split) needs no merge launch
-  RV_HIP(rv::launch_attention(a, p.grid, rv::plan_splits_units(p), rv::plan_long_chunks(p, n_tokens), s), "attention launch");
+  RV_HIP(rv::launch_attention(a, p.grid, rv::plan_splits_units(p), rv::plan_long_chunks(p), s), "attention launch");
 
   if (saliency) {
     rv::AdmitArgs b{};

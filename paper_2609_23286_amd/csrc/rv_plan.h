@@ -211,19 +211,18 @@ AttnPlan plan_attention(int n_cus, int n_queues, int n_tokens, int n_fkeys, int6
 // Whether some unit's key range is split over several chunks (then a merge launch runs).
 bool plan_splits_units(const AttnPlan& p);
 
-// Whether the forward kernel for long chunks is the faster one: the plan's chunks hold enough
-// tiles on average, and its 64-query blocks waste no 32 queries where the units are cut into
-// equal pieces.  Measured against the other kernel (time of the step): +1 to +3 % at 30-50
-// tiles a chunk, 0 at 58, -2 to -5 % at 90-116, -4 to -9 % at 230-300 (1041, 1374, 1200 tokens,
-// 16 heads; 1041 tokens, 12 heads); equal pieces -3 % at 1024 tokens, -1 % at 500, but +1 % at
-// 900 and +0.4 % at 2000, whose last 64-query block is at most half full (stream-K plans gain
-// more than that from the order their chunks take the tiles in: first_tile).
+// Whether the forward kernel for long chunks is the faster one: a stream-K plan whose chunks
+// hold enough tiles on average.  Measured against the other kernel (time of the step, launches
+// back to back): stream-K plans of 90 to 100 tiles a chunk 0 to -7 % (640 to 2048 tokens, 4 to
+// 16 heads), longer ones -1 to -7 %, 30 to 50 tiles +1 to +3 %, 58 tiles 0.  Plans that cut the
+// units into equal pieces 0 to +4 % at 88 to 230 tiles (500 to 2048 tokens, 4 to 16 heads): in
+// them the other kernel's chunks share their keys in L2 as well, which is most of what
+// first_tile gains here.
 constexpr int kLongChunkTiles = 88;
-inline bool plan_long_chunks(const AttnPlan& p, int n_tokens) {
-  if ((int64_t)p.n_units * p.T < (int64_t)kLongChunkTiles * p.total_chunks) return false;
+template <class P>
+inline bool plan_long_chunks(const P& p) {
   const bool pieces = p.n_first == 0 && (int64_t)p.U * kCutScale % p.E == 0;
-  const int last = n_tokens % 64;
-  return !(pieces && last > 0 && last <= 32);
+  return !pieces && (int64_t)p.n_units * p.T >= (int64_t)kLongChunkTiles * p.total_chunks;
 }
 
 // Partial slots a plan writes into: two per chunk (a chunk's segment of the unit it starts

@@ -80,6 +80,7 @@ def _load():
         "rv_admit_staged_layers": ([i32, vp, vp, i32, P(rv_qsub), i32, vp, i32, vp, vp, vp], i32),
         "rv_reserve_workspace": ([i32, i32, i64, i32], i32),
         "rv_attention_plan": ([i32, i32, i64, i32, i32, i32, P(rv_attn_plan)], i32),
+        "rv_attention_plan_long": ([P(rv_attn_plan)], i32),
         "rv_device_status": ([], i32),
     }
     for name, (args, res) in sigs.items():
@@ -180,6 +181,12 @@ def attention_plan(n_tokens, n_fkeys, mem_len, n_heads, n_cus, n_queues):
     out = rv_attn_plan()
     _check(_lib.rv_attention_plan(n_tokens, n_fkeys, mem_len, n_heads, n_cus, n_queues, ctypes.byref(out)))
     return out
+
+
+def attention_plan_long(plan):
+    """Whether a launch of this rv_attn_plan takes the forward kernel for long chunks
+    (rv_attention_plan_long)."""
+    return bool(_lib.rv_attention_plan_long(ctypes.byref(plan)))
 
 
 def device_status():

@@ -111,6 +111,28 @@ def test_aligned_plans_start_every_unit_at_a_chunk_boundary(M, monkeypatch):
                 assert a // p.T == (b - 1) // p.T, (q, c, a, b)
 
 
+LONG_CASES = [  # (N, M, H, overrides, whether the plan takes the kernel for long chunks)
+    # the benchmark's contexts up to the longest of the 1000-frame stream, and above the line
+    (1041, 0, 16, {}, False), (1041, 9990, 16, {}, False), (1041, 18000, 16, {}, False), (1041, 20000, 16, {}, True),
+    (1041, 52000, 16, {}, True), (1374, 19987, 16, {}, True),
+    # either side of 88 tiles a chunk: two chunks for the three units of a queue, 59 and 58 tiles each
+    (128, 3648, 24, {"RV_ATTN_SPLIT": "0", "RV_ATTN_MIN_CHUNK": "89", "RV_ATTN_FIRST_PCT": "100"}, True),
+    (128, 3584, 24, {"RV_ATTN_SPLIT": "0", "RV_ATTN_MIN_CHUNK": "87", "RV_ATTN_FIRST_PCT": "100"}, False),
+    # equal pieces, whatever their length: by the default plan and forced, one piece a unit too
+    (1024, 52000, 16, {}, False), (2048, 52000, 16, {}, False), (704, 44000, 12, {}, False),
+    (1041, 52000, 16, {"RV_ATTN_SPLIT": "3"}, False), (1041, 52000, 16, {"RV_ATTN_SPLIT": "1"}, False),
+]
+
+
+@pytest.mark.parametrize("N,M,H,env,expect", LONG_CASES)
+def test_long_chunk_kernel_is_taken_by_long_stream_k_plans(N, M, H, env, expect, monkeypatch):
+    for k in ENV_KEYS:
+        monkeypatch.delenv(k, raising=False)
+    for k, v in env.items():
+        monkeypatch.setenv(k, v)
+    assert rv.attention_plan_long(rv.attention_plan(N, N, M, H, 256, 8)) is expect
+
+
 def test_plan_rejects_bad_sizes():
     for args in ((0, 0, 0, 16, 256, 8), (1041, 1042, 0, 16, 256, 8), (1041, 1041, -1, 16, 256, 8),
                  (1041, 1041, 0, 0, 256, 8), (1041, 1041, 0, 16, 0, 8), (1041, 1041, 0, 16, 256, 17)):
