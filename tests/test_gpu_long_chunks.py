@@ -6,7 +6,7 @@ import pytest
 
 import oracle
 from paper_2609_23286_amd import synth
-from util import LSE_ATOL, OUT_ATOL, bf16_to_f64, out_error_bound, to_dev, to_host_u16
+from util import LSE_ATOL, OUT_ATOL, SAL_RTOL, bf16_to_f64, out_error_bound, to_dev, to_host_u16
 
 pytestmark = pytest.mark.gpu
 
@@ -85,3 +85,71 @@ def test_long_chunks_match_oracle(N, H, M, split, min_chunk, first_pct, keys, mo
     if keys == "flat":
         assert np.abs(got - want).max() <= OUT_ATOL
     assert np.abs(got_lse - want_lse).max() <= LSE_ATOL + z_err
+
+
+ENTRY_CASES = [  # (N, H, M): the staged frame's last tile ends in the first key half, at a tile
+                 # boundary, in the second half; M a multiple of 64 (the frame path's tiles)
+    (180, 2, 11300), (176, 2, 11344), (150, 3, 11350), (200, 2, 11328),
+]
+
+
+@pytest.mark.parametrize("N,H,M", ENTRY_CASES)
+def test_every_attention_entry_point_takes_long_chunks(N, H, M, monkeypatch):
+    """Two chunks of 88 tiles or more a unit through rv_attend_frame, _noalloc, _fused and
+    rv_attend_staged: the outputs within the oracle's bounds; the frame path's outputs bit for
+    bit from the three calls that take the same plan, from a second call, and from the staged
+    frame where it has the same tiles; the fused saliency rows against the oracle's."""
+    import ctypes
+
+    import torch
+
+    from paper_2609_23286_amd import rv
+
+    print(f"long chunks, entry points N={N} H={H} M={M}", flush=True)
+    rv.init()
+    monkeypatch.setenv("RV_ATTN_SPLIT", "0")
+    monkeypatch.setenv("RV_ATTN_MIN_CHUNK", "91")
+    monkeypatch.setenv("RV_ATTN_FIRST_PCT", "100")
+    for n_fkeys, mem_len in ((N, M), (0, M + N)):
+        p = rv.attention_plan(N, n_fkeys, mem_len, H, 256, 8)
+        assert rv.attention_plan_long(p) and p.total_chunks == 2 * p.n_units
+    Q, K, V = (synth.normal_bf16(41 + N, 0, 0, tag, (N, H, 64), 0.125) for tag in range(3))
+    memK, memV = (synth.normal_bf16(42 + N, 1, 0, tag, (H, M, 64), 0.125) for tag in (synth.TAG_MEMK, synth.TAG_MEMV))
+    mem = rv.Memory(H, reserve_tokens=M + N)
+    mem.write(torch.from_numpy(memK.view(np.int16)), torch.from_numpy(memV.view(np.int16)))
+    Qd, Kd, Vd = to_dev(Q), to_dev(K), to_dev(V)
+    qs = (1, N, 0, 3)
+    got = {}
+    for name in ("frame", "again", "noalloc", "fused", "staged"):
+        out = torch.full((N, H, 64), 3, dtype=torch.int16, device="cuda")
+        lse = torch.full((H, N), -9.0, dtype=torch.float32, device="cuda")
+        if name in ("frame", "again"):
+            rv.attend_frame(Qd, Kd, Vd, mem, out, lse)
+        elif name == "noalloc":
+            vp = ctypes.c_void_p
+            mk, mv, hs = mem.view()
+            st = rv.lib().rv_attend_frame_noalloc(
+                vp(Qd.data_ptr()), vp(Kd.data_ptr()), vp(Vd.data_ptr()), N, vp(mk), vp(mv), M, hs, H, 64, None,
+                vp(out.data_ptr()), vp(lse.data_ptr()), None, vp(torch.cuda.current_stream().cuda_stream))
+            assert st == rv.RV_OK, rv.lib().rv_last_error()
+        elif name == "fused":
+            tiles = torch.full((H, -(-N // 128), N), -1.0, dtype=torch.float32, device="cuda")
+            rv.attend_frame_fused(Qd, Kd, Vd, mem, out, lse, tiles, qs)
+        else:
+            mem.stage_frame(Kd, Vd)
+            rv.attend_staged(Qd, mem, out, lse)
+        rv.device_status()
+        got[name] = (out, lse)
+    mem.close()
+    want, want_lse = oracle.attend(Q, K, V, memK, memV, M)
+    vmax = max(np.abs(bf16_to_f64(V)).max(), np.abs(bf16_to_f64(memV)).max())
+    for name, (out, lse) in got.items():
+        assert np.abs(bf16_to_f64(to_host_u16(out)) - want).max() <= min(OUT_ATOL, out_error_bound(want, vmax)), name
+        assert np.abs(lse.cpu().numpy() - want_lse).max() <= LSE_ATOL, name
+        if name != "staged" or M % 64 == 0:
+            assert torch.equal(out, got["frame"][0]) and torch.equal(lse, got["frame"][1]), name
+    rows, sampled = tiles.cpu().numpy().astype(np.float64), oracle.qsub_index(*qs)
+    for b in range(rows.shape[1]):
+        sel = sampled[(sampled >= 128 * b) & (sampled < 128 * (b + 1))]
+        ref = oracle.column_mass(Q, sel, want_lse[:, sel], K, "frame")
+        assert (np.abs(rows[:, b] - ref) <= SAL_RTOL * ref).all(), f"block {b}"
