@@ -45,10 +45,14 @@ CSRC = os.path.join(ROOT, "paper_2609_23286_amd", "csrc")
 # other sources are stale and are not reported.
 _HOST = ("rv_internal.h", "rv_plan.h", "rv_plan.cpp", "rv_host.cpp")
 KERNEL_SOURCES = {"attn_fwd_kernel": ("attend.hip",) + _HOST,
+                  "attn_long_kernel": ("attend.hip",) + _HOST,
                   "attn_merge_kernel": ("attend.hip",) + _HOST,
                   "sal_kernel": ("admit.hip",) + _HOST,
+                  "sal_one_kernel": ("admit.hip",) + _HOST,
                   "select_kernel": ("admit.hip",) + _HOST}
-ADMISSION_KERNELS = ("sal_kernel", "select_kernel")  # one launch each per frame
+# One launch of either kernel per attention step, and per frame's saliency (the plan decides).
+FORWARD_KERNELS = ("attn_fwd_kernel", "attn_long_kernel")
+SALIENCY_KERNELS = ("sal_kernel", "sal_one_kernel")
 COPY_CALIBRATION_BYTES = 256 << 20   # read and written once by the calibration copy
 WARMUP_MIN_S = 0.1                   # least wall time of warm-up frames (when --warmup > 0)
 
@@ -119,10 +123,23 @@ def recorded_traffic(kernel, workload):
     return None if rec is None else rec[0]
 
 
+def recorded_family(kernels, workload):
+    """(HBM bytes per launch, dispatches counted) over kernels that do the same step, those
+    of them that the workload runs."""
+    recs = [r for r in (recorded_counters(k, workload) for k in kernels) if r is not None]
+    n = sum(r[1] for r in recs)
+    return (sum(r[0] * r[1] for r in recs) / n, n) if n else None
+
+
+def kernel_name(name):
+    """A kernel's own name in a profiler's."""
+    return name.replace("rv::(anonymous namespace)::", "").replace("(anonymous namespace)::", "").split("(")[0]
+
+
 def attention_traffic(workload):
     """HBM bytes of one layer's attention step: the forward launch plus, averaged over
     the stream, the merge launch that split plans add."""
-    fwd, merge = recorded_counters("attn_fwd_kernel", workload), recorded_counters("attn_merge_kernel", workload)
+    fwd, merge = recorded_family(FORWARD_KERNELS, workload), recorded_counters("attn_merge_kernel", workload)
     if fwd is None or merge is None:
         return None
     return fwd[0] + merge[0] * merge[1] / fwd[1]
@@ -130,8 +147,8 @@ def attention_traffic(workload):
 
 def admission_traffic(workload):
     """HBM bytes of one frame's admission (one saliency and one selection launch)."""
-    parts = [recorded_traffic(k, workload) for k in ADMISSION_KERNELS]
-    return None if any(p is None for p in parts) else sum(parts)
+    sal, sel = recorded_family(SALIENCY_KERNELS, workload), recorded_traffic("select_kernel", workload)
+    return None if sal is None or sel is None else sal[0] + sel
 
 
 def bench_args():
@@ -157,7 +174,7 @@ def timed_start(dispatches, steps, layers):
     when steps or layers is not given or the run has fewer launches."""
     if not steps or not layers:
         return None
-    attn = sorted(t for n, t in dispatches if "attn_fwd_kernel" in n)
+    attn = sorted(t for n, t in dispatches if kernel_name(n) in FORWARD_KERNELS)
     if len(attn) < steps * layers:
         return None
     t0 = attn[-steps * layers]
@@ -204,18 +221,22 @@ def summarize_pmc(fetch_dir, write_dir, workload, steps=None, layers=None):
     fetch = per_kernel(timed_counter_rows(f_rows, steps, layers), "FETCH_SIZE")
     write = per_kernel(timed_counter_rows(w_rows, steps, layers), "WRITE_SIZE")
 
-    def find(d, key):
-        hits = [v for k, v in d.items() if key in k]
+    def find(d, key, by=lambda k, key: kernel_name(k) == key):
+        hits = [v for k, v in d.items() if by(k, key)]
         if not hits:
             raise SystemExit(f"no dispatch of {key} in the counter CSVs")
         return hits[0]
 
     copy_key = "neg_kernel"
-    cf = max(find(fetch_all, copy_key))
-    cw = max(find(write_all, copy_key))
+    cf = max(find(fetch_all, copy_key, lambda k, key: key in k))
+    cw = max(find(write_all, copy_key, lambda k, key: key in k))
     f_scale = COPY_CALIBRATION_BYTES / (cf * 1024.0)
     w_scale = COPY_CALIBRATION_BYTES / (cw * 1024.0)
+    ran = {kernel_name(k) for k in fetch}
     for kernel in KERNEL_SOURCES:
+        family = next((f for f in (FORWARD_KERNELS, SALIENCY_KERNELS) if kernel in f), ())
+        if kernel not in ran and any(k in ran for k in family):
+            continue  # (another kernel of the step ran in its place)
         fv, wv = find(fetch, kernel), find(write, kernel)
         f_kib, w_kib = sum(fv) / len(fv), sum(wv) / len(wv)
         total = f_kib * 1024.0 * f_scale + w_kib * 1024.0 * w_scale
@@ -265,8 +286,8 @@ MFMA_PASSES = (("SQ_VALU_MFMA_BUSY_CYCLES", "SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_
 MI355X_XCDS, MI355X_SIMDS = 8, 1024    # 8 XCDs x 32 CUs x 4 SIMDs
 
 
-def mfma_path(workload):
-    return os.path.join(PROFILES, f"attn_fwd_kernel__{workload}__mfma.md")
+def mfma_path(kernel, workload):
+    return os.path.join(PROFILES, f"{kernel}__{workload}__mfma.md")
 
 
 def summarize_mfma(dir_a, dir_b, dir_c, bench_json, workload):
@@ -279,7 +300,7 @@ def summarize_mfma(dir_a, dir_b, dir_c, bench_json, workload):
     def per_kernel(d):
         out = {}
         for r in timed_counter_rows(counter_rows(d), bench["steps"], bench["config"].get("layers")):
-            name = r["Kernel_Name"].replace("rv::(anonymous namespace)::", "").split("(")[0]
+            name = kernel_name(r["Kernel_Name"])
             out.setdefault(name, {}).setdefault(r["Counter_Name"], []).append(float(r["Counter_Value"]))
             if r["Counter_Name"] == "GRBM_GUI_ACTIVE":
                 out[name].setdefault("duration_ns", []).append(
@@ -341,13 +362,17 @@ def summarize_mfma(dir_a, dir_b, dir_c, bench_json, workload):
                      f"{100 * r['valu']:.1f} % | {r['mfma']:.0f} | {r['flops']:.3e} | {r['vinst']:.0f} | "
                      f"{r['trans']:.0f} | {100 * r['issuing']:.0f} % | {100 * r['waiting']:.0f} % | "
                      f"{100 * r['ready']:.0f} % | {100 * r['ldsconf']:.0f} % |")
-    f = rows.get("attn_fwd_kernel")
+    forward = [k for k in FORWARD_KERNELS if k in rows]
+    main_kernel = max(forward, key=lambda k: rows[k]["n"] * rows[k]["dur"], default=FORWARD_KERNELS[0])
+    f = rows.get(main_kernel)
     if f:
+        executed = sum(rows[k]["n"] * rows[k]["flops"] for k in forward) / sum(rows[k]["n"] for k in forward)
         alg = bench["roofline"]["algorithmic_flops_per_launch"]
-        lines += ["", "The attention forward kernel against the benchmark line of the same command (its kernel-trace",
+        lines += ["", "The attention forward kernel" + (f" (`{main_kernel}`)" if main_kernel != "attn_fwd_kernel" else "")
+                  + " against the benchmark line of the same command (its kernel-trace",
                   "run, whose line is not distorted by counter collection):", "",
                   f"- algorithmic flops per launch (4 x 64 per query-key pair): {alg:.4e}; bf16 MFMA flops "
-                  f"executed per dispatch: {f['flops']:.4e} (x{f['flops'] / alg:.3f}: query tiles padded to 128 "
+                  f"executed per dispatch: {executed:.4e} (x{executed / alg:.3f}: query tiles padded to 128 "
                   "rows and key tiles to 64)",
                   f"- executed MFMA work {100 * f['busy24']:.1f} % of the dense peak over the dispatch's own "
                   f"duration; matrix core busy {100 * f['busy']:.1f} % of SIMD cycles; a vector instruction issued in "
@@ -359,8 +384,8 @@ def summarize_mfma(dir_a, dir_b, dir_c, bench_json, workload):
                   f"{100 * bench['roofline']['frac']:.1f} % of {bench['roofline']['peak']} TFLOP/s for the "
                   f"attention step (forward + merge launches, {bench['roofline']['avg_launch_us']:.1f} us per "
                   "layer by HIP events)",
-                  f"- source_hash: {kernel_source_hash('attn_fwd_kernel')}"]
-    path = mfma_path(workload)
+                  f"- source_hash: {kernel_source_hash(main_kernel)}"]
+    path = mfma_path(main_kernel, workload)
     with open(path, "w") as fh:
         fh.write("\n".join(lines) + "\n")
     print(f"wrote {path}")
@@ -376,17 +401,13 @@ def summarize_trace(trace_dir, bench_json, workload):
         raise SystemExit(f"no kernel_trace.csv under {trace_dir}")
     bench = json.loads(open(bench_json).read().strip().splitlines()[-1])
 
-    def short(name):
-        name = name.replace("rv::(anonymous namespace)::", "").replace("(anonymous namespace)::", "")
-        return name.split("(")[0]
-
     disp = [(r["Kernel_Name"], int(r["Start_Timestamp"]), int(r["End_Timestamp"]))
             for r in csv.DictReader(open(traces[0]))]
     t0 = timed_start([(n, t) for n, t, _ in disp], bench["steps"], bench["config"].get("layers"))
     durs = {}
     for n, t, e in disp:
         if t0 is None or t >= t0:
-            durs.setdefault(short(n), []).append(e - t)
+            durs.setdefault(kernel_name(n), []).append(e - t)
     grand = sum(sum(v) for v in durs.values()) or 1
     rows = sorted(({"Name": k, "Calls": len(v), "TotalDurationNs": sum(v), "AverageNs": sum(v) / len(v),
                     "Percentage": 100.0 * sum(v) / grand, "MinNs": min(v), "MaxNs": max(v)}
@@ -394,9 +415,12 @@ def summarize_trace(trace_dir, bench_json, workload):
     avg = {r["Name"]: r["AverageNs"] / 1e3 for r in rows}
     total = {r["Name"]: r["TotalDurationNs"] / 1e3 for r in rows}
     calls = {r["Name"]: r["Calls"] for r in rows}
-    # One attention step = attn_fwd_kernel, plus attn_merge_kernel for a split plan.
-    attn_step = ((total.get("attn_fwd_kernel", 0.0) + total.get("attn_merge_kernel", 0.0))
-                 / max(calls.get("attn_fwd_kernel", 1), 1))
+    # One attention step = a forward kernel, plus attn_merge_kernel for a split plan.
+    ran = lambda kernels: [k for k in kernels if k in calls] or [kernels[0]]
+    family_avg = lambda kernels: sum(total.get(k, 0.0) for k in kernels) / max(sum(calls.get(k, 0) for k in kernels), 1)
+    forward, saliency = ran(FORWARD_KERNELS), ran(SALIENCY_KERNELS)
+    attn_step = (family_avg(forward) + total.get("attn_merge_kernel", 0.0)
+                 / max(sum(calls.get(k, 0) for k in forward), 1))
     lines = [f"# Kernel time summary: {workload} benchmark", "",
              "Command (on the MI355X, from the repository root):", "", "```",
              "cd /tmp && export TMPDIR=/tmp",
@@ -410,16 +434,17 @@ def summarize_trace(trace_dir, bench_json, workload):
     for r in rows:
         lines.append(f"| `{r['Name']}` | {r['Calls']} | {int(r['TotalDurationNs'])} | "
                      f"{r['AverageNs']:.0f} | {r['Percentage']:.2f} | {r['MinNs']} | {r['MaxNs']} |")
-    adm = sum(avg.get(k, 0.0) for k in ADMISSION_KERNELS)
+    adm = family_avg(saliency) + avg.get("select_kernel", 0.0)
+    either = " or ".join(forward)
     lines += ["", "The same run's benchmark line (HIP events on the compute stream):", "",
               f"- frames/s: {bench['value']:.1f}",
               f"- attention: {bench['roofline']['avg_launch_us']:.1f} us per layer step (events around "
               f"the forward launch and, for split plans, the merge launch) vs {attn_step:.1f} us "
-              f"(rocprofv3: attn_fwd_kernel + attn_merge_kernel time per attn_fwd_kernel call; "
-              f"attn_fwd_kernel alone averages {avg.get('attn_fwd_kernel', 0.0):.1f} us)",
+              f"(rocprofv3: {either} + attn_merge_kernel time per {either} call; "
+              + ", ".join(f"{k} alone averages {avg.get(k, 0.0):.1f} us" for k in forward) + ")",
               f"- admission: {bench['phases']['admission_ms'] / bench['steps'] * 1e3:.1f} us per frame (events; "
               f"the pair also spans the launch gaps) vs {adm:.1f} us (rocprofv3 averages of "
-              + " + ".join(ADMISSION_KERNELS) + ")",
+              + " or ".join(saliency) + " + select_kernel)",
               f"- attention roofline: {bench['roofline']['achieved']:.1f} TFLOP/s = "
               f"{100 * bench['roofline']['frac']:.1f} % of {bench['roofline']['peak']}"]
     path = os.path.join(PROFILES, f"kernel_trace__{workload}.md")
@@ -1081,6 +1106,14 @@ def main():
         f"({admit_ms / n_timed * 1e3:.1f} us/frame, {admit_gbs:.0f} GB/s)")
 
     mean_ctx = sum(mem_len(l, t) + N for t in timed for l in range(L)) / n_attn
+    # the kernels of the timed frames, by their plans
+    plan_of = (lambda m: (N, 0, m + N)) if args.staged else (lambda m: (N, N, m))
+    n_cus = torch.cuda.get_device_properties(dev).multi_processor_count
+    longs = {rv.attention_plan_long(rv.attention_plan(*plan_of(m), H, n_cus, MI355X_XCDS))
+             for m in {mem_len(l, t) for t in timed for l in range(L)}}
+    forward_name = " / ".join(k for k, taken in zip(FORWARD_KERNELS, (False in longs, True in longs)) if taken)
+    one_fits = len(regulated) * H * -(-N // 128) <= 4 * n_cus  # (a launch that may take one key block a wave)
+    saliency_name = " / ".join(SALIENCY_KERNELS) if one_fits else SALIENCY_KERNELS[0]
     if full:
         sampling = f"the whole {n_stream}-frame stream in order from "
         sampling += f"{cfg.prefill} prefilled memory rows" if cfg.prefill else "empty memory"
@@ -1111,14 +1144,14 @@ def main():
                    "regulated_layers": len(regulated), "anchor": anchor,
                    "selection": "head-averaged" if args.shared else "head-specific",
                    "staged_frames": bool(args.staged), "prefill_rows": cfg.prefill},
-        "roofline": {"kernel": "attn_fwd_kernel (+ attn_merge_kernel on split plans)", "bound": "mfma",
+        "roofline": {"kernel": f"{forward_name} (+ attn_merge_kernel on split plans)", "bound": "mfma",
                      "achieved": achieved_tf,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s", "frac": achieved_tf / PEAK_BF16_TFLOPS,
                      "traffic": attention_traffic(wkey) if wkey else None,
                      "avg_launch_us": attn_avg_s * 1e6,
                      "algorithmic_flops_per_launch": flops / n_attn},
         "phases": {"attention_ms": attn_ms, "admission_ms": admit_ms, "staging_ms": stage_ms,
-                   "admission_roofline": {"kernel": "sal_kernel + select_kernel", "bound": "hbm",
+                   "admission_roofline": {"kernel": f"{saliency_name} + select_kernel", "bound": "hbm",
                                           "achieved": admit_gbs,
                                           "peak": PEAK_HBM_GBS, "unit": "GB/s",
                                           "frac": admit_gbs / PEAK_HBM_GBS,

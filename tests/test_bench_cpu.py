@@ -170,3 +170,43 @@ def test_profile_summaries_keep_the_timed_frames_dispatches():
     kept = bench.timed_counter_rows(rows, 2, 2)
     assert len(kept) == 2 * 9 and min(int(r["Start_Timestamp"]) for r in kept) == 20
     assert bench.timed_counter_rows(rows, None, None) == rows
+
+
+def test_profile_summaries_know_the_other_kernel_of_a_step(tmp_path, monkeypatch):
+    """A workload whose steps take attn_long_kernel (in part) and sal_one_kernel: the window of
+    the timed frames, the step's time per forward launch, and the traffic averaged over both
+    forward kernels.  The epilogue's attn_merge_sal_kernel is not taken for sal_kernel."""
+    import json
+    monkeypatch.setattr(bench, "PROFILES", str(tmp_path))
+    d = [("attn_long_kernel", 10), ("attn_fwd_kernel", 12), ("attn_long_kernel", 20), ("attn_fwd_kernel", 22),
+         ("attn_long_kernel", 30), ("attn_long_kernel", 32)]
+    assert bench.timed_start(d, 2, 2) == 20
+    full = "rv::(anonymous namespace)::{}(rv::Args)".format
+    trace = [("attn_long_kernel", 100), ("attn_merge_kernel", 5), ("attn_fwd_kernel", 60), ("attn_merge_kernel", 5),
+             ("attn_merge_sal_kernel", 9), ("sal_one_kernel", 8), ("select_kernel", 4)]
+    at, lines = 1000, ["Kernel_Name,Start_Timestamp,End_Timestamp"]
+    for k, us in [("attn_long_kernel", 700)] + trace:      # a warm-up launch, then one frame of two layers
+        lines.append(f"{full(k)},{at},{at + 1000 * us}")
+        at += 1000 * us
+    (tmp_path / "t").mkdir()
+    (tmp_path / "t" / "x_kernel_trace.csv").write_text("\n".join(lines) + "\n")
+    line = {"steps": 1, "config": {"layers": 2}, "value": 1.0, "phases": {"admission_ms": 0.02},
+            "roofline": {"avg_launch_us": 90.0, "achieved": 1.0, "frac": 0.1, "peak": 10.0}}
+    (tmp_path / "b.json").write_text(json.dumps(line))
+    bench.summarize_trace(str(tmp_path / "t"), str(tmp_path / "b.json"), "w")
+    text = (tmp_path / "kernel_trace__w.md").read_text()
+    assert "vs 85.0 us" in text and "vs 12.0 us" in text and "700000" not in text
+    assert "attn_long_kernel alone averages 100.0 us" in text and "sal_one_kernel + select_kernel" in text
+    header = "Dispatch_Id,Kernel_Name,Counter_Name,Counter_Value,Start_Timestamp,End_Timestamp\n"
+    kib = {"attn_long_kernel": (100.0, 10.0), "attn_fwd_kernel": (40.0, 10.0), "attn_merge_kernel": (4.0, 1.0),
+           "attn_merge_sal_kernel": (999.0, 999.0), "sal_one_kernel": (20.0, 2.0), "select_kernel": (3.0, 1.0)}
+    runs = ["attn_long_kernel", "attn_long_kernel", "attn_long_kernel"] + list(kib)[1:]
+    for counter, sub, col in (("FETCH_SIZE", "fetch", 0), ("WRITE_SIZE", "write", 1)):
+        (tmp_path / sub).mkdir()
+        rows = [f"1,neg_kernel,{counter},{bench.COPY_CALIBRATION_BYTES / 1024.0},0,1"]
+        rows += [f"{i + 2},{full(k)},{counter},{kib[k][col]},0,1" for i, k in enumerate(runs)]
+        (tmp_path / sub / "c_counter_collection.csv").write_text(header + "\n".join(rows) + "\n")
+    bench.summarize_pmc(str(tmp_path / "fetch"), str(tmp_path / "write"), "w")
+    assert not (tmp_path / "sal_kernel__w__hbm_traffic.md").exists()
+    assert bench.attention_traffic("w") == pytest.approx(((3 * 110 + 50) / 4 + 5 / 4) * 1024)
+    assert bench.admission_traffic("w") == pytest.approx((22 + 4) * 1024)
