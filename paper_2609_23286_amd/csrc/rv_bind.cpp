@@ -8,6 +8,7 @@
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/version.h>
 
 #include <cstdint>
 #include <exception>
@@ -163,4 +164,11 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_rv_bind", nullptr, -1, kMethods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__rv_bind(void) { return PyModule_Create(&kModule); }
+// built_for: the torch and Python whose headers this was compiled with.  It reads their
+// objects directly, so rv.py loads it with the same ones only.
+PyMODINIT_FUNC PyInit__rv_bind(void) {
+  PyObject* m = PyModule_Create(&kModule);
+  if (m && PyModule_AddObject(m, "built_for", Py_BuildValue("(sii)", TORCH_VERSION, PY_MAJOR_VERSION, PY_MINOR_VERSION)))
+    Py_CLEAR(m);
+  return m;
+}

@@ -11,6 +11,8 @@ import of this module fails.
 import ctypes
 import importlib.util
 import os
+import re
+import sys
 
 import torch
 
@@ -93,9 +95,17 @@ def _load():
 def _load_bind():
     if not os.path.exists(BIND_PATH):
         raise ImportError(f"{BIND_PATH} is not built; run __graft_entry__.build()")
+    here = (re.match(r"[\d.]+\d", torch.__version__).group(), *sys.version_info[:2])
     spec = importlib.util.spec_from_file_location("paper_2609_23286_amd._rv_bind", BIND_PATH)
-    mod = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(mod)
+    try:
+        mod = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(mod)
+        built_for = mod.built_for
+    except (ImportError, AttributeError) as e:
+        built_for = e
+    if built_for != here:
+        raise ImportError(f"{BIND_PATH} was built for another torch or Python than {here}: {built_for}; "
+                          "run __graft_entry__.build()")
     return mod
 
 
@@ -112,9 +122,15 @@ def _check(status):
         raise RVError(status, _lib.rv_last_error().decode(errors="replace"))
 
 
+# (the same handle as torch.cuda.current_stream().cuda_stream, without the stream object: 1 us a call)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream):
     if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        if _raw_stream is None:
+            return torch.cuda.current_stream().cuda_stream
+        return _raw_stream(torch.cuda.current_device())
     if isinstance(stream, torch.cuda.Stream):
         return ctypes.c_void_p(stream.cuda_stream)
     return ctypes.c_void_p(int(stream))

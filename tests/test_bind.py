@@ -77,3 +77,25 @@ def test_closed_memory_is_refused():
     m.handle, m.n_heads = None, 2
     want = outcome(rv.Memory.view, m)
     assert want[0] is rv.RVError and outcome(rv._mem_state, m) == want
+
+
+def test_another_torch_or_a_broken_module_is_refused(tmp_path, monkeypatch):
+    assert torch.__version__.startswith(rv._load_bind().built_for[0])
+    with monkeypatch.context() as m:
+        m.setattr(torch, "__version__", "1.0.0+rocm7.0")
+        with pytest.raises(ImportError, match=r"built for another torch.*1\.0\.0.*build\(\)"):
+            rv._load_bind()
+    (tmp_path / "_rv_bind.so").write_bytes(b"not a module")
+    monkeypatch.setattr(rv, "BIND_PATH", str(tmp_path / "_rv_bind.so"))
+    with pytest.raises(ImportError, match=r"build\(\)"):
+        rv._load_bind()
+
+
+@pytest.mark.gpu
+def test_default_stream_is_the_current_one(monkeypatch):
+    s = torch.cuda.Stream()
+    for raw in (rv._raw_stream, None):      # (with and without the short way)
+        monkeypatch.setattr(rv, "_raw_stream", raw)
+        assert rv._stream(None) == torch.cuda.current_stream().cuda_stream
+        with torch.cuda.stream(s):
+            assert rv._stream(None) == s.cuda_stream
