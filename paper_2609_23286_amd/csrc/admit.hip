@@ -479,10 +479,11 @@ static_assert(40 + kRankedTokens / 24 <= kRankedBudget && kRankedBudget <= NT, "
 // Candidates that are ranked, at most: one a thread.  (More would take a second round of counts:
 // 256 candidates at budget 10 take 11 us, 320 take 16, as long as the radix way after the attempt.)
 constexpr int kMaxCandidates = NT;
-// Equal values from which they are cut to those needed.  (It takes about 2.5 us, as long as
-// counting over 100 more candidates.  All tokens equal, 1041 tokens: 8.8 us at budget 1, 9.3 at
-// 10; without the cut, through the radix way, 15.5 and 15.2.)
-constexpr int kManyEqual = 64;
+// Candidates past twice the budget from which the equal ones among them are looked at, and equal
+// ones past those needed from which they are cut.  (The cut takes about 2.5 us, as long as counting
+// over 100 more candidates.  All tokens equal, 1041 tokens: 8.6 us at budget 1, 9.2 at 10; without
+// the cut, through the radix way, 15.5 and 15.2.)
+constexpr int kManyMore = 64;
 
 // Top-`budget` (takes_ranked), ascending, into s_idx; v[m] is the value of token tid + NT m.  The
 // budget-th largest of the 256 threads' maxima is no larger than the budget-th largest value, so
@@ -503,7 +504,7 @@ __device__ __forceinline__ bool select_ranked(const float (&v)[kLaneSlots], int 
   __shared__ uint32_t s_sorted[NT];
   __shared__ int32_t s_win[kRankedBudget];
   __shared__ uint32_t s_bound;
-  __shared__ int s_count[3];  // tokens at or above the bound | equal ones << 16; candidates; tokens above the bound
+  __shared__ int s_count[3];  // tokens at or above the bound; above it; candidates
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t best = 0u;  // (threads without tokens rank last: budget < N)
 #pragma unroll
@@ -531,15 +532,13 @@ __device__ __forceinline__ bool select_ranked(const float (&v)[kLaneSlots], int 
   if (rank == budget - 1) s_bound = x;
   __syncthreads();
   const uint32_t bound = s_bound;
-  // (bit m: the thread's m-th token)
-  uint32_t above = 0u, equal = 0u;
+  uint32_t in = 0u;  // the thread's tokens at or above the bound, a bit each
 #pragma unroll
-  for (int m = 0; m < kLaneSlots; ++m) {
-    const uint32_t b = __float_as_uint(v[m]);
-    above |= (uint32_t)(tid + NT * m < N && b > bound) << m;
-    equal |= (uint32_t)(tid + NT * m < N && b == bound) << m;
-  }
-  auto gather = [&](uint32_t in, int at) {
+  for (int m = 0; m < kLaneSlots; ++m)
+    in |= (uint32_t)(tid + NT * m < N && __float_as_uint(v[m]) >= bound) << m;
+  auto gather = [&](int* count) {
+    if (in == 0u) return;
+    int at = atomicAdd(count, __popc(in));
 #pragma unroll
     for (int m = 0; m < kLaneSlots; ++m)
       if (in >> m & 1u) {
@@ -547,41 +546,41 @@ __device__ __forceinline__ bool select_ranked(const float (&v)[kLaneSlots], int 
         ++at;
       }
   };
-  if (above | equal)
-    gather(above | equal, atomicAdd(&s_count[0], __popc(above | equal) + (__popc(equal) << 16)) & 0xFFFF);
+  gather(&s_count[0]);
   __syncthreads();
-  int nc = s_count[0] & 0xFFFF;
-  const int n_equal = s_count[0] >> 16;
-  if (nc > 2 * budget && n_equal > kManyEqual) {  // uniform
+  int nc = s_count[0];
+  if (nc > 2 * budget + kManyMore) {  // uniform
     int n_above = 0;
 #pragma unroll
     for (int m = 0; m < kLaneSlots; ++m) {
-      const uint64_t eq = __ballot(equal >> m & 1u);
-      n_above += __popcll(__ballot(above >> m & 1u));
-      if (lane == 0) s_equal[m * NW + wave] = eq;  // tokens NT m + 64 wave ..
+      const bool eq = (in >> m & 1u) && __float_as_uint(v[m]) == bound;
+      const uint64_t word = __ballot(eq);
+      n_above += __popcll(__ballot(in >> m & 1u)) - __popcll(word);
+      if (lane == 0) s_equal[m * NW + wave] = word;  // tokens NT m + 64 wave ..
     }
-    if (lane == 0 && n_above) atomicAdd(&s_count[2], n_above);
+    if (lane == 0 && n_above) atomicAdd(&s_count[1], n_above);
     __syncthreads();
-    const int need = budget - s_count[2];
-    // Equal tokens before word l, on lane l.
-    const int own = lane < kLaneSlots * NW ? __popcll(s_equal[lane]) : 0;
-    int before = own;
+    const int above = s_count[1], need = max(0, budget - above);
+    if (nc - above > need + kManyMore) {  // uniform
+      // Equal tokens before word l, on lane l.
+      const int own = lane < kLaneSlots * NW ? __popcll(s_equal[lane]) : 0;
+      int before = own;
 #pragma unroll
-    for (int off = 1; off < kLaneSlots * NW; off <<= 1) {
-      const int u = __shfl_up(before, off);
-      if (lane >= off) before += u;
-    }
-    before -= own;
-    uint32_t in = above;
+      for (int off = 1; off < kLaneSlots * NW; off <<= 1) {
+        const int u = __shfl_up(before, off);
+        if (lane >= off) before += u;
+      }
+      before -= own;
 #pragma unroll
-    for (int m = 0; m < kLaneSlots; ++m) {
-      const int first = __shfl(before, m * NW + wave);
-      const uint64_t word = s_equal[m * NW + wave];
-      if ((equal >> m & 1u) && first + __popcll(word & ((1ull << lane) - 1)) < need) in |= 1u << m;
+      for (int m = 0; m < kLaneSlots; ++m) {
+        const int first = __shfl(before, m * NW + wave);
+        const uint64_t word = s_equal[m * NW + wave];
+        if ((word >> lane & 1u) && first + __popcll(word & ((1ull << lane) - 1)) >= need) in &= ~(1u << m);
+      }
+      gather(&s_count[2]);
+      __syncthreads();
+      nc = s_count[2];
     }
-    if (in) gather(in, atomicAdd(&s_count[1], __popc(in)));
-    __syncthreads();
-    nc = s_count[1];
   }
   if (nc > cap) {  // uniform
     __syncthreads();  // (s_cand is the caller's again)

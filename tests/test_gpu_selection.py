@@ -24,7 +24,7 @@ CASES = [  # (N, budget, values)
     (80, 41, "spread"), (2, 1, "zero"),
     # equal values cut to those the budget needs: in every word of 64 tokens, in the last one only,
     # more values above the bound than the budget (threads hold several), and none needed
-    (2048, 125, "half equal"), (2047, 1, "equal"), (2048, 70, "zero"), (2040, 60, "last equal"),
+    (2048, 125, "half equal"), (2047, 1, "equal"), (2048, 70, "zero"), (2040, 20, "last equal"),
     (2048, 40, "clump equal"),
     # more candidates than fit, none of them equal
     (2048, 52, "clump"), (1041, 83, "clump"),
@@ -52,10 +52,10 @@ def saliency(N, values, rng):
         s = np.full(N, 0.25)
     elif values == "zero":
         s = np.zeros(N)
-    elif values == "last equal":    # 58 spread ones, and the last 60 tokens equal
+    elif values == "last equal":    # 18 spread ones, and the last 150 tokens equal
         s = rng.random(N) * 0.5
-        s[rng.choice(N - 60, 58, replace=False)] = 2.0 + rng.random(58)
-        s[N - 60 + rng.choice(60, 60, replace=False)] = 1.0
+        s[rng.choice(N - 150, 18, replace=False)] = 2.0 + rng.random(18)
+        s[N - 150:] = 1.0
     elif values in ("clump", "clump equal"):    # all of the largest values on fewer threads than the budget
         s = rng.random(N) * 0.5 + (np.arange(N) % 256 < (51 if values == "clump" else 30))
         if values == "clump equal":             # ... and the bound a value that 200 others hold
