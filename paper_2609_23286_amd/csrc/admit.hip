@@ -269,9 +269,9 @@ __device__ __forceinline__ void sal_body(const AdmitArgs& a, unsigned char* smem
 
 // Blocks a wave takes at a time: two, or one (sal_one_kernel) where no range holds more than a
 // block a wave (launches of few layers: the wave's chain of query blocks is what the launch waits for,
-// and half as long with one).  Saliency and selection back to back, two -> one: one layer of
-// 1041 tokens 14.5 -> 12.3 us, 4 layers 16.5 -> 15.6, two layers with every patch sampled 33.3
-// -> 26.8.  (One instantiation for both made the launch of 24 layers 0.9 % longer.)
+// and half as long with one).  Saliency alone, two -> one: one layer of 1041 tokens, 16 heads
+// 10.4 -> 8.0 us, 4 layers 12.6 -> 11.6; with every patch sampled one layer 29.0 -> 21.4, 4 layers
+// 34.6 -> 30.9.  (One instantiation for both made the launch of 24 layers 0.9 % longer.)
 __global__ __launch_bounds__(NT, 3) void sal_kernel(AdmitArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   if (a.stage_queries)
@@ -495,9 +495,9 @@ constexpr int kManyMore = 64;
 // every thread, if there are more than `cap` candidates.
 // What bounds it is the chain of dependent steps, one wave per SIMD.  (Before: `budget`
 // rounds of wave-wide maxima in each wave and again over their winners, or, above 32, the
-// radix select.  The selection launch for 24 layers of 1041 tokens: 9.7 -> 5.9 us at budget
-// 10, 15.0 -> 10.4 at 52; one layer 8.4 -> 5.6; an empty launch takes 2.4.  Reading eight
-// keys a step in the counts: 6.6 and 12.1.)
+// radix select.  The selection launch for 24 layers of 1041 tokens: 8.8 -> 5.2 us at budget
+// 10, 12.6 -> 6.1 at 20, 13.0 -> 8.4 at 52; one layer 7.4 -> 5.2; an empty launch takes 2.4.
+// Reading eight keys a step in the counts was slower by a tenth.)
 __device__ __forceinline__ bool select_ranked(const float (&v)[kLaneSlots], int N, int budget, int32_t* s_idx,
                                               uint64_t* s_cand, int cap) {
   __shared__ uint64_t s_equal[kLaneSlots * NW];  // tokens equal to the bound, a bit each, in order
@@ -620,8 +620,8 @@ __global__ __launch_bounds__(NT) void select_kernel(AdmitArgs a) {
   // The saliency that is ranked: the sum, in order, of n_rows rows of N values -- the head's
   // row; its per-block rows (computed in the attention epilogue: the sum is the saliency,
   // written out when asked for); or all heads' rows.  Tokens j0 + NT m, with kLaneSlots *
-  // kRowBatch loads in flight (token by token, eight rows at a time, the per-block rows of
-  // 1041 tokens took the launch 11.8 us instead of 7.4).
+  // kRowBatch loads in flight (token by token, eight rows at a time, the nine per-block rows of
+  // 1041 tokens took the launch of 7 layers 10.8 us instead of 6.9).
   const int n_rows = a.shared_select ? H : a.sal_tiles > 0 ? a.sal_tiles : 1;
   const float* const rows = a.shared_select ? L.sal : L.sal + (int64_t)h_own * n_rows * N;
   auto values = [&](int j0, float (&acc)[kLaneSlots]) {

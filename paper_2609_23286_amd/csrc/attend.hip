@@ -503,12 +503,15 @@ __device__ void process_segment(const AttnArgs& a, int q, int c, int unit, int u
 // before run under each block's exponentials.  The two key halves meet in LDS at a segment's
 // end.
 //
-// What bounds it is the card's power: it runs at about 2.05 GHz with data like the streams'
-// and at 2.4 GHz with zeros.  Against attn_fwd_kernel the launch takes 10 % fewer cycles and
-// 3-8 % less time where a chunk holds 90 tiles or more (1041 tokens, 16 heads: 20,000 rows
-// 107-109 -> 104-106 us, 52,000 rows 249-259 -> 243-246; 1374 tokens: 20,000 rows 138 -> 131,
-// 52,000 rows 338 -> 309), the same at 40 to 60, and up to 2.5 us more below: the longer
-// prologue, the exchange at the end and odd tiles (1041 tokens, empty memory: 15.3 -> 17.5).
+// The matrix core is busy 44 % of the cycles, the vector ALU 58 %; waves wait for 21 % of theirs
+// and hold an instruction that does not issue for 29 %; and the clock is at about 2.1 GHz with
+// data like the streams' (2.4 with zeros).  Against attn_fwd_kernel (53,300 keys, 1041 tokens, 16
+// heads) the launch takes 4.20 M cycles over the XCDs instead of 4.45 M, and 245 us instead of
+// 254.  On stream-K plans of 90 tiles a chunk or more the step takes 0 to 7 % less (16 heads, 1041
+// tokens: 20,000 rows 106 -> 106 us, 52,000 rows 253 -> 249-251; 1374 tokens: 20,000 rows 136 ->
+// 133, 52,000 rows 326 -> 305; 12 heads, 1041 tokens, 52,000 rows 206 -> 194), the same at 40 to
+// 60, and up to 2.5 us more below: the longer prologue, the exchange at the end and odd tiles
+// (1041 tokens, empty memory: 15.3 -> 17.5).
 // Added to the scores of keys past a tile's end.  Scaled, it lies below kNegBig, the lowest
 // softmax reference here as in attn_fwd_kernel, so that a wave whose 32 keys are all masked
 // gets p = 0 for each.
