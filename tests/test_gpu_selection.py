@@ -12,12 +12,12 @@ CASES = [  # (N, budget, values)
     # fewer tokens than threads, one wave's worth, exactly 256 and one to either side
     (2, 1, "spread"), (3, 2, "spread"), (63, 10, "spread"), (65, 32, "spread"), (255, 128, "spread"),
     (256, 128, "spread"), (257, 127, "spread"),
-    # the largest ranked frame and budget, and one past each
+    # budgets past the line of the largest ranked frame, one token past it, the smallest budget
     (2048, 128, "spread"), (2048, 129, "spread"), (2049, 128, "spread"), (2047, 1, "spread"),
     # all of the largest values on one thread, and on one wave
     (1041, 5, "one thread"), (1041, 40, "one wave"), (1041, 64, "descending"), (1041, 64, "ascending"),
-    # ties: few levels (more candidates than fit: the radix way), half the tokens equal at
-    # the bound, all equal, all zero, zeros below a few values
+    # ties: few levels, half the tokens equal at the bound, all equal, all zero (by radix), zeros
+    # below a few values
     (1041, 10, "levels"), (1041, 52, "half equal"), (1041, 10, "equal"), (200, 128, "zero"), (1041, 52, "few"),
     # the largest budget that is ranked for a frame, and one more (40 + N / 24; half the tokens)
     (1041, 83, "spread"), (1041, 84, "spread"), (2048, 125, "spread"), (2048, 126, "spread"), (80, 40, "spread"),
@@ -98,8 +98,9 @@ def test_selection_edges(N, budget, values):
 @pytest.mark.parametrize("grid,special,stride,layers", [
     ((28, 37), 5, 2, 24),   # one block a wave alone, two in 24 layers
     ((28, 37), 5, 1, 8),    # several passes of staged query rows; 8 layers: past the line
-    ((28, 37), 5, 2, 7),    # 7 layers: the last shape with one block a wave
-    ((12, 11), 1, 3, 24),   # 5 blocks: ranges of 4 and 1
+    ((28, 37), 5, 2, 6),    # 6 layers: two a wave, in one round of workgroups
+    ((28, 37), 5, 2, 7),    # 7 layers: one a wave, two rounds either way
+    ((12, 11), 1, 3, 24),   # 5 blocks: ranges of 3 and 2
     ((8, 8), 0, 2, 24),     # 2 blocks for 4 waves
 ])
 def test_saliency_bits_do_not_depend_on_the_launch(grid, special, stride, layers):
