@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 CASES = [  # (N, budget, values)
     # fewer tokens than threads, one wave's worth, exactly 256 and one to either side
     (2, 1, "spread"), (3, 2, "spread"), (63, 10, "spread"), (65, 32, "spread"), (255, 128, "spread"),
-    (256, 128, "spread"), (257, 127, "spread"),
+    (256, 128, "spread"), (257, 127, "spread"), (255, 50, "spread"), (256, 50, "spread"), (257, 50, "spread"),
     # budgets past the line of the largest ranked frame, one token past it, the smallest budget
     (2048, 128, "spread"), (2048, 129, "spread"), (2049, 128, "spread"), (2047, 1, "spread"),
     # all of the largest values on one thread, and on one wave
